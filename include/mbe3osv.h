@@ -406,9 +406,10 @@ int64_t mbe3_screen_noalloc_max_bytes(void);
  * (i n_occ + j) n_atom + A): the charges of the localized orbitals; U device
  * [n_occ][n_occ] row-major: the localized orbitals are C~ U; dL and
  * rotations host [max_sweeps] (nullable): each sweep's sum and rotation
- * count; *sweeps (host) the sweeps run.  One workgroup runs the sweeps (the
- * pairs are sequential: each rotation changes what the next pair reads).
- * Allocates two small device buffers per call and synchronises `stream`.
+ * count; *sweeps (host) the sweeps run.  The pairs of one antidiagonal i + j
+ * share no orbital and turn together, from the charges the pairs in order
+ * would give them.  Allocates n_occ^2 doubles and, while P takes at most
+ * 64 MiB, a second P per call, and synchronises `stream` after every sweep.
  * MBE3_EINVAL for bad sizes or offsets (message from mbe3_last_error(NULL)),
  * MBE3_ENOCONV when max_sweeps end above l_loc (outputs valid),
  * MBE3_ENONFINITE for a non-finite increment.

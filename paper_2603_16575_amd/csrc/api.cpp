@@ -2084,26 +2084,41 @@ int mbe3_pm_localize(const double *C, const int32_t *ao_off, int32_t n_ao, int32
       return fail(MBE3_EINVAL, "mbe3_pm_localize: ao_off must not decrease");
   hipStream_t st = (hipStream_t)stream;
   int32_t *d_off = nullptr;
-  double *d_rec = nullptr;
+  double *d_ws = nullptr, *d_p2 = nullptr;
   auto release = [&] {
     if (d_off) (void)hipFree(d_off);
-    if (d_rec) (void)hipFree(d_rec);
+    if (d_ws) (void)hipFree(d_ws);
+    if (d_p2) (void)hipFree(d_p2);
   };
-  std::vector<double> rec((size_t)2 * max_sweeps + 1, 0.0);
+  const size_t p_bytes = sizeof(double) * (size_t)n_occ * n_occ * n_atom;
+  const int64_t nws = pm_ws_doubles(n_occ);
   hipError_t e = hipMalloc((void **)&d_off, sizeof(int32_t) * ((size_t)n_atom + 1));
-  if (e == hipSuccess) e = hipMalloc((void **)&d_rec, sizeof(double) * rec.size());
+  if (e == hipSuccess) e = hipMalloc((void **)&d_ws, sizeof(double) * (size_t)(nws + 2));
+  if (e == hipSuccess && pm_two_buffers(n_occ, n_atom)) e = hipMalloc((void **)&d_p2, p_bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     release();
     return fail(MBE3_ENOMEM, "mbe3_pm_localize: device allocation failed");
   }
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d_off, ao_off, sizeof(int32_t) * ((size_t)n_atom + 1),
-                       hipMemcpyHostToDevice, st);
+  e = hipMemcpyAsync(d_off, ao_off, sizeof(int32_t) * ((size_t)n_atom + 1),
+                     hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = launch_pm_charges(C, d_off, n_occ, n_atom, P, st);
-  if (e == hipSuccess) e = launch_pm_jacobi(P, U, n_occ, n_atom, l_loc, max_sweeps, d_rec, st);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(rec.data(), d_rec, sizeof(double) * rec.size(), hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = launch_pm_identity(U, n_occ, st);
+  int ns = 0;
+  double last[2] = {0.0, 0.0};
+  double *p0 = P, *p1 = d_p2;  // the charges, the other buffer
+  while (e == hipSuccess && ns < max_sweeps && (ns == 0 || last[0] > l_loc)) {
+    e = launch_pm_sweep(&p0, &p1, U, n_occ, n_atom, d_ws, d_ws + nws, st);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(last, d_ws + nws, sizeof last, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) break;
+    if (dL) dL[ns] = last[0];
+    if (rotations) rotations[ns] = (int32_t)last[1];
+    ++ns;
+  }
+  if (e == hipSuccess && p0 != P)
+    e = hipMemcpyAsync(P, p0, p_bytes, hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   release();
   if (e != hipSuccess) {
@@ -2111,15 +2126,10 @@ int mbe3_pm_localize(const double *C, const int32_t *ao_off, int32_t n_ao, int32
     snprintf(buf, sizeof buf, "mbe3_pm_localize: %s", hipGetErrorString(e));
     return fail(MBE3_EHIP, buf);
   }
-  const int ns = (int)rec[2 * (size_t)max_sweeps];
   *sweeps = ns;
-  for (int k = 0; k < ns; ++k) {
-    if (dL) dL[k] = rec[2 * (size_t)k];
-    if (rotations) rotations[k] = (int32_t)rec[2 * (size_t)k + 1];
-  }
-  if (ns > 0 && !std::isfinite(rec[2 * (size_t)(ns - 1)]))
+  if (!std::isfinite(last[0]))
     return fail(MBE3_ENONFINITE, "mbe3_pm_localize: non-finite increment");
-  if (ns > 0 && rec[2 * (size_t)(ns - 1)] > l_loc)
+  if (last[0] > l_loc)
     return fail(MBE3_ENOCONV, "mbe3_pm_localize: max_sweeps reached above l_loc");
   g_create_error = "ok";
   return MBE3_OK;

@@ -109,12 +109,17 @@ hipError_t launch_rosv_finalize(const double *evals, int D, const double *Qr,
 
 // Pipek-Mezey localization (loc.hip): Loewdin charges P[(i n + j) na + A]
 // from orthonormalized MO coefficients C [n_ao][n] with the AOs of atom A at
-// ao_off[A] .. ao_off[A+1]-1 (device), and the Jacobi sweeps of one
-// workgroup (rec: 2 doubles per sweep, then the sweep count).
+// ao_off[A] .. ao_off[A+1]-1 (device); U = 1; one Jacobi sweep (rec: the summed
+// increment and the rotation count).  The sweep's charges move between *P and
+// *P2 (swapped on return if they ended in the other one) when *P2 is given
+// (pm_two_buffers), else they stay in *P.  ws: pm_ws_doubles(n) doubles.
 hipError_t launch_pm_charges(const double *C, const int32_t *ao_off, int n, int na, double *P,
                              hipStream_t s);
-hipError_t launch_pm_jacobi(double *P, double *U, int n, int na, double l_loc, int max_sweeps,
-                            double *rec, hipStream_t s);
+hipError_t launch_pm_identity(double *U, int n, hipStream_t s);
+int64_t pm_ws_doubles(int n);
+bool pm_two_buffers(int n, int na);
+hipError_t launch_pm_sweep(double **P, double **P2, double *U, int n, int na, double *ws,
+                           double *rec, hipStream_t s);
 
 // Split-precision operands (regen.hip): three bf16 planes (bit patterns),
 // plane stride ps elements, rows padded with zeros to ldk (a multiple of 8).
