@@ -1025,6 +1025,8 @@ int build_plans(mbe3_handle *h) {
     for (int tl = 0; tl < fd.nt; ++tl) {
       const int t = ls[tl];
       const int p = h->sp[t], q = h->sq[t];
+      fd.tb[tl] = (int)terms.size() - fd.term_begin;
+      fd.tg[tl] = fd.tb[tl];  // a diagonal target's terms mirror its pairs'
       if (p == q) {
         for (int k : F) {
           if (k == p) continue;
@@ -1047,6 +1049,7 @@ int build_plans(mbe3_handle *h) {
         terms.push_back(tm);
         tm.src = local(p, p); tm.st_off = st_ut(t, p);
         terms.push_back(tm);
+        fd.tg[tl] += 2;
         for (int r : F) {
           if (r == p || r == q) continue;
           // first sum, k = r: f_pr S_(pq,rq) T_rq S_(rq,pq)
@@ -1056,16 +1059,21 @@ int build_plans(mbe3_handle *h) {
           a.target = tl; a.src = lrq; a.fx = p; a.fy = r;
           a.trans = r > q ? 1 : 0; a.st_buf = 1;
           a.st_off = cross[lrq][tl];
-          terms.push_back(a);
           // second sum, k = r: f_rq S_(pq,pr) T_pr S_(pr,pq)
           Term b;
           std::memset(&b, 0, sizeof b);
           b.target = tl; b.src = lpr; b.fx = r; b.fy = q;
           b.trans = p > r ? 1 : 0; b.st_buf = 1;
           b.st_off = cross[lpr][tl];
-          terms.push_back(b);
+          // each of the three couplings between the trimer's pairs (3, 4, 5)
+          // is the gradient pass's once: 3 from 4, 4 from 5, 5 from 3
+          const bool a_first = lrq == (tl == 5 ? 3 : tl + 1);
+          terms.push_back(a_first ? a : b);
+          terms.push_back(a_first ? b : a);
+          fd.tg[tl] += 1;
         }
       }
+      fd.te[tl] = (int)terms.size() - fd.term_begin;
     }
     fd.term_end = (int)terms.size();
     fds.push_back(fd);
@@ -1471,6 +1479,16 @@ int validate_plans(mbe3_handle *h) {
       if (fd.term_begin < 0 || fd.term_end < fd.term_begin || fd.term_end > (int)terms.size())
         return bad("solve (terms)", k);
       if (fd.term_end - fd.term_begin > MAX_FRAG_TERMS) return bad("solve (term count)", k);
+      for (int l = 0, at = 0; l < fd.nt; ++l) {
+        if (fd.tb[l] != at || fd.tg[l] < at || fd.te[l] < fd.tg[l] ||
+            fd.te[l] > fd.term_end - fd.term_begin)
+          return bad("solve (term ranges)", k);
+        for (int e = fd.tb[l]; e < fd.te[l]; ++e)
+          if (terms[fd.term_begin + e].target != l) return bad("solve (term target)", k);
+        at = fd.te[l];
+        if (l + 1 == fd.nt && at != fd.term_end - fd.term_begin)
+          return bad("solve (term ranges)", k);
+      }
       for (int l = 0; l < fd.nt; ++l) {
         const int s = fd.slot[l];
         if (s < 0 || s >= h->n_slot) return bad("solve (slot)", k);
@@ -1530,10 +1548,16 @@ int build_grad_plans(mbe3_handle *h) {
         if (fd.yout < 0 || fd.yout + fd.ysub[l] + D * D > ch.ny_total) return bad("Y store", k);
         bs[sl].push_back({fd.yout + fd.ysub[l], fd.coef});
       }
-      for (int e = fd.term_begin; e < fd.term_end; ++e) {
-        const Term &t = terms[e];
-        gs[t.fx * n + t.fy].push_back({-fd.coef * fd.wgt[t.target], 0, e});
-      }
+      // the coupling operator is symmetric: the contraction of a term
+      // (target from source) equals its mirror's (source from target; twice
+      // it where the mirror is a diagonal target of half the weight), and f
+      // is symmetrised afterwards, so each coupling is contracted once and
+      // counts twice
+      for (int l = 0; l < fd.nt; ++l)
+        for (int e = fd.term_begin + fd.tb[l]; e < fd.term_begin + fd.tg[l]; ++e) {
+          const Term &t = terms[e];
+          gs[t.fx * n + t.fy].push_back({-2.0 * fd.coef * fd.wgt[l], 0, e});
+        }
       // f_pp and f_qq inside E~ (both f_pp for a diagonal slot)
       for (int l = 0; l < fd.nt; ++l) {
         const int sl = fd.slot[l];
@@ -2313,7 +2337,7 @@ int fragment_solve(mbe3_handle *h, const double *K, double *e_frag,
         PhaseScope ps_(h, MBE3_PHASE_SOLVE);
         HIP_TRY(h, launch_solve(a, nwg, s));
       }
-      if (W) {  // dE/df contractions and Y~ at the converged amplitudes
+      if (W) {  // dE/df contractions at the converged amplitudes
         HIP_TRY(h, solve_blocks_per_cu(a, 2, &per_cu_g));
         per_cu_g = std::max(1, per_cu_g);
         const int nwg_g = std::min(std::min(SOLVE_WG, c.n_frag), 256 * per_cu_g);
@@ -2336,6 +2360,7 @@ int fragment_solve(mbe3_handle *h, const double *K, double *e_frag,
   if (W) {
     PhaseScope ps_(h, MBE3_PHASE_GRAD);
     b.p[B_W] = W;
+    HIP_TRY(h, launch_wtilde_finish(h->d_slots, h->n_slot, h->wt, s));
     HIP_TRY(h, launch_list(h, h->L_wm, b, s));
     HIP_TRY(h, launch_list(h, h->L_ww, b, s));
   }

@@ -14,7 +14,7 @@
 
 namespace mbe3 {
 
-// W~_slot += sum_entries c Y~ (Y~ = 2Y - Y^T stored by the solver), one
+// V_slot += sum_entries c Y (the converged amplitudes the solver stored), one
 // workgroup per work item (an element range of a slot); every element sums
 // its entries in fragment order.  A thread keeps WT_J elements in registers
 // and reads WT_U entries ahead before adding them in order, so that each
@@ -72,6 +72,29 @@ hipError_t launch_wtilde(const WSlot *slots, int n_slots, const WEntry *ents,
   if (n_slots <= 0) return hipSuccess;
   hipLaunchKernelGGL(wtilde_kernel, dim3(n_slots), dim3(256), 0, s, slots, ents,
                      yfin, wt);
+  return hipGetLastError();
+}
+
+// W~ = 2 V - V^T: taken once per slot, so that the store holds Y as the solver
+// wrote it and no pass over it has to form 2Y - Y^T.
+__global__ __launch_bounds__(256) void wtilde_finish_kernel(const SlotInfo *__restrict__ slots,
+                                                            double *__restrict__ wt) {
+  const SlotInfo sl = slots[blockIdx.x];
+  double *w = wt + sl.kt_off;
+  const int D = sl.D;
+  for (int e = threadIdx.x; e < D * D; e += 256) {
+    const int i = e / D, j = e - i * D;
+    if (j < i) continue;
+    const double a = w[i * D + j], b = w[j * D + i];
+    w[i * D + j] = 2.0 * a - b;
+    w[j * D + i] = 2.0 * b - a;
+  }
+}
+
+hipError_t launch_wtilde_finish(const SlotInfo *slots, int64_t n_slot, double *wt,
+                                hipStream_t s) {
+  if (n_slot <= 0) return hipSuccess;
+  hipLaunchKernelGGL(wtilde_finish_kernel, dim3((unsigned)n_slot), dim3(256), 0, s, slots, wt);
   return hipGetLastError();
 }
 

@@ -252,6 +252,8 @@ struct FragDesc {
   int32_t term_begin, term_end;
   int32_t slot[6];      // global slot ids, order: diagonals then pairs
   int32_t ysub[6];      // offset of each slot's D x D block in Y scratch
+  int32_t tb[6], tg[6], te[6];  // slot k's terms: term_begin + [tb, te), of
+                        // which the gradient pass runs [tb, tg)
   int32_t sym[6];       // 1 for diagonal slots (residual symmetrised)
   int32_t wgt[6];       // energy weight 1 (diagonal) or 2 (pair)
   int32_t ny;           // sum of D^2 over the fragment's slots
@@ -292,19 +294,17 @@ struct SolveArgs {
   int32_t *iters;
   int32_t *status;       // [2 * workgroup]: non-finite seen, non-converged seen
   double *warm;          // converged Y per slot (K~ layout), or null
-  // gradient mode (all null otherwise): Y~ = 2Y - Y^T of the converged
-  // blocks per fragment (at FragDesc::yout; the LDS-resident solver stores Y
-  // there and its gradient pass turns it into Y~), per-term contractions
-  // <Y~_t, S~ Y_s^(T) S~^T> (<Y_t + Y_t^T, .> for diagonal targets) indexed
-  // by term, and per-target <Y~_t, Y_t> at 6 * fragment + target.
+  // gradient mode (all null otherwise): the converged Y blocks per fragment
+  // (at FragDesc::yout), the contractions <Y~_t, S~ Y_s^(T) S~^T>, Y~ = 2Y -
+  // Y^T, of the terms FragDesc::tg names, indexed by term, and per-target
+  // <Y~_t, Y_t> at 6 * fragment + target.
   double *yfin;
   double *gterm;
   double *gdiag;
 };
 hipError_t launch_solve(const SolveArgs &a, int n_wg, hipStream_t s);
 // The gradient pass over a chunk that launch_solve solved with yfin set (the
-// same arguments and grid): per-term contractions, <Y~_t, Y_t>, and Y~ into
-// the store.
+// same arguments and grid): per-term contractions and <Y~_t, Y_t>.
 hipError_t launch_solve_grad(const SolveArgs &a, int n_wg, hipStream_t s);
 // Variant for 96 < dmax <= 160 (solve_wide.hip): one wave per 16-row block,
 // panels streamed for both products, per-workgroup term sums in the scratch
@@ -321,8 +321,8 @@ size_t solve_lds_bytes(int dmax);
 // ---------------------------------------------------------------------------
 // Backward (backward.hip)
 // ---------------------------------------------------------------------------
-// W~ of one slot (D x D at wt_off) += sum of its entries [e_begin, e_end).
-// One work item of the W~ reduction: elements [y0, y0 + n) of a slot's
+// One work item of the W~ reduction (the sum of c_F Y over a slot's entries):
+// elements [y0, y0 + n) of a slot's
 // D x D block, summed over the entries [e_begin, e_end) (a slot in many
 // fragments is split over several items by element range).
 struct WSlot {
@@ -330,11 +330,15 @@ struct WSlot {
   int32_t n, e_begin, e_end, y0;
 };
 struct WEntry {
-  int64_t yoff;  // converged Y~ = 2Y - Y^T block (D x D) in the chunk's store
+  int64_t yoff;  // converged Y block (D x D) in the chunk's store
   double coef;   // c_F
 };
 hipError_t launch_wtilde(const WSlot *slots, int n_slots, const WEntry *ents,
                          const double *yfin, double *wt, hipStream_t s);
+// W~ = 2 V - V^T of every slot, in place, once all chunks' sums V = sum_F c_F Y
+// are in.
+hipError_t launch_wtilde_finish(const SlotInfo *slots, int64_t n_slot, double *wt,
+                                hipStream_t s);
 // g[dst] += sum of scale * (kind ? gdiag[idx] : gterm[idx]) over the entries
 // (one wave per destination, lane-strided partial sums, fixed shuffle tree).
 struct GDest {

@@ -77,6 +77,7 @@ struct SlotLds {
   int64_t kt_off, et_off;
   double fpq;  // f_pp + f_qq
   int32_t D, ysub, sym, wgt;
+  int32_t tb, te;  // the terms this launch runs for the slot
 };
 
 // Sum / max of the per-wave partials r[0 .. N) as a fixed tree: the first
@@ -150,7 +151,7 @@ __device__ __forceinline__ double wg_sum(double v, double *red) {
       /* the next panel streams in under the products; a term's last panel   \
          prefetches the next term's first one */                              \
       MBE3_ADVANCE();                                                          \
-      if (p_ti < f_te) MBE3_LOAD_PANEL();                                      \
+      if (p_tl < f_nt) MBE3_LOAD_PANEL();                                      \
       __syncthreads();                                                         \
       const double *STp = Sl + 16 * mp * Dt;                                   \
       _Pragma("unroll") for (int mm = 0; mm < 4; ++mm) {                       \
@@ -189,11 +190,15 @@ __device__ __forceinline__ double wg_sum(double v, double *red) {
 // MODE 0: solve.  MODE 1: solve and store each converged fragment's Y at
 // FragDesc::yout (zero if it converged at T = 0) for the gradient pass.
 // MODE 2: the gradient pass alone, a separate launch over the same
-// fragments: the stored Y goes back into the scratch, every term's product
-// is formed once more with unit coefficient and contracted with Y~, and the
-// store then receives Y~ = 2Y - Y^T for the multipliers.  Fragments that did
-// not converge (iters < 0) are skipped.  Keeping the pass out of the solving
-// launch keeps its registers out of the iterations.
+// fragments: the terms [tb, tg) of each pair target are formed once more from
+// the stored Y with unit coefficient and contracted with Y~ = 2Y - Y^T.  The
+// coupling operator is symmetric, so a term's contraction equals its mirror's
+// (source and target exchanged) up to the pair weights, and 9 of a trimer's 18
+// terms are enough; of each couple the one with the wider target runs, which
+// leaves fewer waves without a row block.  Measured at 160 orbitals (90k
+// fragments): 29.8 ms for 59.8 ms with every term.  Fragments that did not
+// converge (iters < 0) are skipped.  Keeping the pass out of the solving launch keeps its
+// registers out of the iterations.
 template <int MAXNT, int MODE, int NW>
 __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(SolveArgs a) {
   constexpr bool ST = MODE == 1, GP = MODE == 2;
@@ -257,27 +262,26 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
       c.ysub = fdp->ysub[tl];
       c.sym = fdp->sym[tl];
       c.wgt = fdp->wgt[tl];
+      c.tb = f_tb + fdp->tb[tl];
+      c.te = f_tb + (GP ? fdp->tg[tl] : fdp->te[tl]);
       sc[tl] = c;
     }
     __syncthreads();
     if (GP) {
-      // the pass reads the stored Y in place; the contraction weights of
-      // every target (Y + Y^T for a diagonal one, else 2Y - Y^T = Y~) go to
-      // the second scratch buffer, Y~ of the diagonal targets to the third,
-      // and <Y~_t, Y_t> to gdiag
+      // the pass reads the stored Y in place; the contraction weights 2Y -
+      // Y^T = Y~ of the pair targets go to the second scratch buffer, and
+      // <Y~_t, Y_t> to gdiag
       for (int tl = 0; tl < f_nt; ++tl) {
         const int D = sc[tl].D;
         const int sy = sc[tl].sym;
         const double *y = a.yfin + fdp->yout + sc[tl].ysub;
         double *wy = Y0 + ny_cap + sc[tl].ysub;
-        double *yd = Y0 + 2 * ny_cap + sc[tl].ysub;
         double part = 0.0;
         for (int e = tid; e < D * D; e += NTH) {
           const int i = e / D, j = e - i * D;
           const double yv = y[e], yt = y[(int64_t)j * D + i];
           const double ytil = 2.0 * yv - yt;
-          wy[e] = sy ? yv + yt : ytil;
-          if (sy) yd[e] = ytil;
+          if (!sy) wy[e] = ytil;
           part += ytil * yv;
         }
         const double tot = wg_sum<NW>(part, red_d);  // also orders the wy writes
@@ -301,7 +305,7 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
       };
 
       // ---- panel pipeline: step (ti, m) = rows 16m.. of S~ and of Y^(T) ----
-      int p_ti = f_tb, p_m = 0;  // step held in pf
+      int p_tl = -1, p_ti = 0, p_end = 0, p_m = 0;  // step held in pf
       int p_n1 = 0, p_n2 = 0;
       bool p_tr = false;  // the Y part of pf is a strip of Y columns
       // descriptors of term c_ti (the one the prefetch is in), read from LDS
@@ -339,12 +343,27 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
       pf[u] = *src_;                                                           \
     }                                                                          \
   } while (0)
+// first term of the next targets that have any (p_tl == f_nt: none left)
+#define MBE3_NEXT_TARGET()                                                     \
+  do {                                                                         \
+    while (p_ti >= p_end && ++p_tl < f_nt) {                                   \
+      p_ti = __builtin_amdgcn_readfirstlane(sc[p_tl].tb);                      \
+      p_end = __builtin_amdgcn_readfirstlane(sc[p_tl].te);                     \
+    }                                                                          \
+  } while (0)
 #define MBE3_ADVANCE()                                                         \
   do {                                                                         \
-    if (++p_m >= (c_ds >> 4)) { p_m = 0; ++p_ti; }                             \
+    if (++p_m >= (c_ds >> 4)) {                                                \
+      p_m = 0;                                                                 \
+      ++p_ti;                                                                  \
+      MBE3_NEXT_TARGET();                                                      \
+    }                                                                          \
   } while (0)
 
-      if (hasY && f_tb < f_te) MBE3_LOAD_PANEL();
+      if (hasY) {
+        MBE3_NEXT_TARGET();
+        if (p_tl < f_nt) MBE3_LOAD_PANEL();
+      }
 
       for (int tl = 0; tl < f_nt; ++tl) {
         const SlotLds sl = sc[tl];
@@ -357,15 +376,14 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
           for (int jb = 0; jb < MAXNT; ++jb) acc[rb][jb] = d4{0.0, 0.0, 0.0, 0.0};
 
         if (hasY) {
-          for (int ti = f_tb; ti < f_te; ++ti) {
-            if (tc[ti - f_tb].target != tl) continue;
+          const int t_end = __builtin_amdgcn_readfirstlane(sl.te);
+          for (int ti = __builtin_amdgcn_readfirstlane(sl.tb); ti < t_end; ++ti) {
             const double coef = tc[ti - f_tb].coef;
             const int Ds = __builtin_amdgcn_readfirstlane(tc[ti - f_tb].ds);
             const int nS = Ds >> 4;
             MBE3_TERM_PRODUCTS(coef);
             if (GP) {
               // this term's product alone, contracted with Y~ = 2Y - Y^T
-              // (Y + Y^T for a diagonal target, whose mirror term is folded)
               const double *Wy = Y0 + ny_cap + sl.ysub;
               double part = 0.0;
 #pragma unroll
@@ -449,15 +467,6 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
         }
       }
       if (GP) {
-        // Y~ over the stored Y (every read of it is done: the last term's
-        // contraction ended in a workgroup barrier, its last panel fetched
-        // nothing further)
-        for (int tl = 0; tl < f_nt; ++tl) {
-          const int D = sc[tl].D;
-          const double *src = Y0 + (sc[tl].sym ? 2 : 1) * ny_cap + sc[tl].ysub;
-          double *o = a.yfin + fdp->yout + sc[tl].ysub;
-          for (int e = tid; e < D * D; e += NTH) o[e] = src[e];
-        }
         __syncthreads();  // the scratch is read; the next fragment refills it
         break;
       }
@@ -517,6 +526,7 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
   }
 }
 #undef MBE3_ADVANCE
+#undef MBE3_NEXT_TARGET
 #undef MBE3_LOAD_PANEL
 #undef MBE3_TERM_PRODUCTS
 

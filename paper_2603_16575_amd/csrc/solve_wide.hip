@@ -116,9 +116,9 @@ void solve_wide_kernel(SolveArgs a) {
         for (int e = tid; e < Dt * Dt; e += NTH) R[e] = 0.0;
         __syncthreads();
         if (hasY) {
-          for (int ti = f_tb; ti < f_te; ++ti) {
+          const int t_end = f_tb + (GRAD && gpass ? fdp->tg[tl] : fdp->te[tl]);
+          for (int ti = f_tb + fdp->tb[tl]; ti < t_end; ++ti) {
             const Term tm = a.terms[ti];
-            if (tm.target != tl) continue;
             const double coef =
                 (GRAD && gpass) ? 1.0 : a.f_occ[(int64_t)tm.fx * a.n_occ + tm.fy];
             const int Ds = a.slots[fdp->slot[tm.src]].D;
@@ -189,15 +189,13 @@ void solve_wide_kernel(SolveArgs a) {
               }
             }
             if (GRAD && gpass) {
-              // this term alone, contracted with Y~ = 2Y - Y^T (Y + Y^T for a
-              // diagonal target, whose mirror term is folded); R cleared again
+              // this term alone, contracted with Y~ = 2Y - Y^T; R cleared again
               __syncthreads();
               const double *Yc = Ycb + fdp->ysub[tl];
               const double *YTc = YTcb + fdp->ysub[tl];
               double part = 0.0;
               for (int e = tid; e < Dt * Dt; e += NTH) {
-                const double wy = sym ? Yc[e] + YTc[e] : 2.0 * Yc[e] - YTc[e];
-                part += wy * R[e];
+                part += (2.0 * Yc[e] - YTc[e]) * R[e];
                 R[e] = 0.0;
               }
               const double tot = wide_sum<NW>(part, red_d);
@@ -291,7 +289,7 @@ void solve_wide_kernel(SolveArgs a) {
             break;
           }
           for (int e = tid; e < fdp->ny; e += NTH)
-            a.yfin[fdp->yout + e] = 2.0 * Ycb[e] - YTcb[e];
+            a.yfin[fdp->yout + e] = Ycb[e];
           __syncthreads();
           gpass = true;
           continue;
