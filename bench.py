@@ -66,14 +66,21 @@ def solve_flops(prob, iters, grad=False, warm=True):
     2 d_t d_s^2 (S~ Y) + 2 d_t^2 d_s (Z S~^T).  A fragment with `iters`
     updates evaluates iters + 1 residuals; from T = 0 the first (R~ = K~)
     needs no product, so `iters` sweeps carry the products; a warm-started
-    trimer's first residual has them too (iters + 1).  With the gradient the
-    converged amplitudes go through the products once more (dE/df)."""
+    trimer's first residual has the products between its pairs (the last six
+    terms), while those within a pair's own fragment are formed once per dimer.
+    With the gradient one term of each mirror couple goes through the products
+    once more (dE/df)."""
     dims = fragment_dims(prob)
     tot = 0.0
+    sums = warm and len(prob.trimers) > 0
     for f, terms, it in zip(prob.frags, dims, iters):
-        per = sum(2.0 * dt * ds * (ds + dt) for dt, ds in terms)
-        sweeps = int(it) + (1 if warm and f[2] >= 0 else 0)
-        tot += per * (sweeps + (1 if grad and sweeps > 0 else 0))
+        fl = [2.0 * dt * ds * (ds + dt) for dt, ds in terms]
+        per, warm_tri = sum(fl), warm and f[2] >= 0
+        tot += per * int(it) + (sum(fl[12:]) if warm_tri else 0.0)
+        if sums and f[1] >= 0 and f[2] < 0:
+            tot += per
+        if grad and (int(it) > 0 or warm_tri):
+            tot += 0.5 * per
     return tot
 
 

@@ -96,6 +96,9 @@ struct mbe3_handle {
   int precision = MBE3_FP64;
   bool warm_start = false;
   double *warm = nullptr;  // converged Y of every slot's own fragment
+  double *base = nullptr;  // coupling sums of every dimer at those amplitudes
+  std::vector<int64_t> base_off;
+  int64_t base_total = 0;
   int ldk_vir = 0, ldk_aux = 0;  // padded row pitch of split planes
   hipStream_t stream = nullptr;
   std::string err;
@@ -1027,6 +1030,7 @@ int build_plans(mbe3_handle *h) {
       const int p = h->sp[t], q = h->sq[t];
       fd.tb[tl] = (int)terms.size() - fd.term_begin;
       fd.tg[tl] = fd.tb[tl];  // a diagonal target's terms mirror its pairs'
+      fd.tx[tl] = p == q ? -1 : fd.tb[tl] + 2;
       if (p == q) {
         for (int k : F) {
           if (k == p) continue;
@@ -1074,6 +1078,7 @@ int build_plans(mbe3_handle *h) {
         }
       }
       fd.te[tl] = (int)terms.size() - fd.term_begin;
+      if (p == q) fd.tx[tl] = fd.te[tl];
     }
     fd.term_end = (int)terms.size();
     fds.push_back(fd);
@@ -1086,11 +1091,23 @@ int build_plans(mbe3_handle *h) {
   if ((rc = dev_alloc(h, &h->st1, max_st1))) return rc;
 
   // ---- slots, energies ----
+  // coupling sums of the dimers whose domains the LDS-resident solver takes,
+  // where warm-started trimers read them
+  h->base_off.assign(h->n_slot, -1);
+  h->base_total = 0;
+  if (h->warm_start && !h->chunks.empty() && is_tri(h->chunks.back().frag_ids.front()))
+    for (int64_t s = n; s < h->n_slot; ++s) {
+      const int64_t D = h->sD[s], Dp = h->sD[h->sp[s]], Dq = h->sD[h->sq[s]];
+      if (D > SOLVE_LDS_DMAX) continue;
+      h->base_off[s] = h->base_total;
+      h->base_total += Dp * Dp + Dq * Dq + D * D;
+    }
   std::vector<SlotInfo> si(h->n_slot);
   for (int64_t s = 0; s < h->n_slot; ++s) {
     si[s].p = h->sp[s]; si[s].q = h->sq[s];
     si[s].d = h->sd[s]; si[s].D = h->sD[s];
     si[s].kt_off = h->kt_off[s]; si[s].et_off = h->et_off[s];
+    si[s].base_off = h->base_off[s];
   }
   if ((rc = upload(h, &h->d_slots, si))) return rc;
   if ((rc = upload(h, &h->d_coef, h->coef))) return rc;
@@ -1168,6 +1185,7 @@ int alloc_workspace(mbe3_handle *h) {
   if ((rc = dev_alloc(h, &h->eig_meta, 4 * h->n_slot))) return rc;
   if ((rc = dev_alloc(h, &h->eig_redo, h->n_slot))) return rc;
   if (h->warm_start && (rc = dev_alloc(h, &h->warm, h->kt_off[h->n_slot]))) return rc;
+  if (h->base_total && (rc = dev_alloc(h, &h->base, h->base_total))) return rc;
   {
     const int md = max_d(h), nl = eig_lds_max_order();
     if (md > nl) {
@@ -1472,6 +1490,7 @@ int validate_plans(mbe3_handle *h) {
   for (size_t c = 0; c < h->h_fds.size(); ++c) {
     const auto &fds = h->h_fds[c];
     const auto &terms = h->h_terms[c];
+    const int dmax_of_chunk = h->chunks[c].dmax;
     for (size_t k = 0; k < fds.size(); ++k) {
       const FragDesc &fd = fds[k];
       if (!(fd.nt == 1 || fd.nt == 3 || fd.nt == 6)) return bad("solve (nt)", k);
@@ -1480,11 +1499,18 @@ int validate_plans(mbe3_handle *h) {
         return bad("solve (terms)", k);
       if (fd.term_end - fd.term_begin > MAX_FRAG_TERMS) return bad("solve (term count)", k);
       for (int l = 0, at = 0; l < fd.nt; ++l) {
-        if (fd.tb[l] != at || fd.tg[l] < at || fd.te[l] < fd.tg[l] ||
-            fd.te[l] > fd.term_end - fd.term_begin)
+        if (fd.tb[l] != at || fd.tg[l] < at || fd.te[l] < fd.tg[l] || fd.tx[l] < at ||
+            fd.te[l] < fd.tx[l] || fd.te[l] > fd.term_end - fd.term_begin)
           return bad("solve (term ranges)", k);
-        for (int e = fd.tb[l]; e < fd.te[l]; ++e)
-          if (terms[fd.term_begin + e].target != l) return bad("solve (term target)", k);
+        for (int e = fd.tb[l]; e < fd.te[l]; ++e) {
+          const Term &t = terms[fd.term_begin + e];
+          if (t.target != l) return bad("solve (term target)", k);
+          if ((t.st_buf != 0) != (e >= fd.tx[l])) return bad("solve (cross terms)", k);
+        }
+        if (fd.warm_in && dmax_of_chunk <= SOLVE_LDS_DMAX && l >= 3 &&
+            (h->base_off[fd.slot[l]] < 0 ||
+             h->base_off[fd.slot[l]] >= h->base_total))
+          return bad("solve (coupling sums)", k);
         at = fd.te[l];
         if (l + 1 == fd.nt && at != fd.term_end - fd.term_begin)
           return bad("solve (term ranges)", k);
@@ -2287,6 +2313,7 @@ int fragment_solve(mbe3_handle *h, const double *K, double *e_frag,
     HIP_TRY(h, launch_fill(h->wt, 0.0, h->kt_off[h->n_slot], s));
     HIP_TRY(h, launch_fill(h->graw, 0.0, (int64_t)h->n_occ * h->n_occ, s));
   }
+  bool base_done = false;
   for (auto &c : h->chunks) {
     if (c.n_asm) {
       PhaseScope ps_(h, MBE3_PHASE_CROSS);
@@ -2317,6 +2344,24 @@ int fragment_solve(mbe3_handle *h, const double *K, double *e_frag,
     a.iters = iters;
     a.status = h->status;
     a.warm = h->warm;
+    a.base = h->base;
+    if (h->base && !base_done && h->frags[c.frag_ids.front()][2] >= 0) {
+      // every monomer and dimer is solved: their coupling sums, once per pair
+      for (auto &d : h->chunks) {
+        if (h->frags[d.frag_ids.front()][2] >= 0 || d.dmax > SOLVE_LDS_DMAX) continue;
+        SolveArgs g = a;
+        g.frags = d.d_frags;
+        g.terms = d.d_terms;
+        g.n_frag = d.n_frag;
+        g.dmax = d.dmax;
+        int per_cu = 0;
+        HIP_TRY(h, solve_blocks_per_cu(g, 3, &per_cu));
+        const int nwg = std::min(std::min(SOLVE_WG, d.n_frag), 256 * std::max(1, per_cu));
+        PhaseScope ps_(h, MBE3_PHASE_SOLVE);
+        HIP_TRY(h, launch_solve_base(g, nwg, s));
+      }
+      base_done = true;
+    }
     if (W) {
       a.yfin = h->yfin;
       a.gterm = h->gterm;

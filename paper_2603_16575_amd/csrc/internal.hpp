@@ -245,6 +245,8 @@ struct SlotInfo {
   int32_t d, D;      // pair-domain dimension and padded X-basis dimension
   int64_t kt_off;    // K~ = X^T K X (D x D) in the K~ store
   int64_t et_off;    // eps~ (D) in the eps~ store
+  int64_t base_off;  // pair slots: coupling sums of the pair's own fragment
+                     // (D_p^2, D_q^2, D^2 doubles), or -1
 };
 struct FragDesc {
   int32_t nt;           // number of pair slots (1, 3 or 6)
@@ -252,8 +254,10 @@ struct FragDesc {
   int32_t term_begin, term_end;
   int32_t slot[6];      // global slot ids, order: diagonals then pairs
   int32_t ysub[6];      // offset of each slot's D x D block in Y scratch
-  int32_t tb[6], tg[6], te[6];  // slot k's terms: term_begin + [tb, te), of
-                        // which the gradient pass runs [tb, tg)
+  int32_t tb[6], tx[6], tg[6], te[6];  // slot k's terms: term_begin + [tb, te);
+                        // from tx on they couple pairs of a trimer, before it
+                        // a pair and one of its orbitals; the gradient pass
+                        // runs [tb, tg)
   int32_t sym[6];       // 1 for diagonal slots (residual symmetrised)
   int32_t wgt[6];       // energy weight 1 (diagonal) or 2 (pair)
   int32_t ny;           // sum of D^2 over the fragment's slots
@@ -294,6 +298,8 @@ struct SolveArgs {
   int32_t *iters;
   int32_t *status;       // [2 * workgroup]: non-finite seen, non-converged seen
   double *warm;          // converged Y per slot (K~ layout), or null
+  double *base;          // coupling sums of the warm store at SlotInfo::base_off
+                         // (launch_solve_base), or null
   // gradient mode (all null otherwise): the converged Y blocks per fragment
   // (at FragDesc::yout), the contractions <Y~_t, S~ Y_s^(T) S~^T>, Y~ = 2Y -
   // Y^T, of the terms FragDesc::tg names, indexed by term, and per-target
@@ -303,6 +309,9 @@ struct SolveArgs {
   double *gdiag;
 };
 hipError_t launch_solve(const SolveArgs &a, int n_wg, hipStream_t s);
+// Coupling sums of a chunk's dimers at the warm store's amplitudes, for the
+// first sweep of the trimers that contain them.
+hipError_t launch_solve_base(const SolveArgs &a, int n_wg, hipStream_t s);
 // The gradient pass over a chunk that launch_solve solved with yfin set (the
 // same arguments and grid): per-term contractions and <Y~_t, Y_t>.
 hipError_t launch_solve_grad(const SolveArgs &a, int n_wg, hipStream_t s);
@@ -313,7 +322,8 @@ hipError_t launch_solve_wide(const SolveArgs &a, int n_wg, hipStream_t s);
 size_t solve_wide_lds_bytes(int dmax);
 constexpr int SOLVE_LDS_DMAX = 128;  // largest dmax of the LDS-resident solver
 // Resident workgroups per CU of the solver instance a chunk with a.dmax
-// runs (mode 0 solve, 1 solve and store, 2 gradient pass).
+// runs (mode 0 solve, 1 solve and store, 2 gradient pass, 3 coupling
+// sums).
 hipError_t solve_blocks_per_cu(const SolveArgs &a, int mode, int *per_cu);
 int64_t solve_scratch_doubles(int ny_max, int dmax);
 size_t solve_lds_bytes(int dmax);
