@@ -27,6 +27,7 @@ namespace {
 
 constexpr int DMAX_SUPPORTED = 160;  // largest padded pair dimension handled
 constexpr int SOLVE_WG = 1024;       // persistent workgroups of the solver
+constexpr int64_t CLASS_MIN_FRAGS = 4096;  // fragments that make a solver class
 constexpr int64_t SLAB_BUDGET = 2LL << 30;    // bytes of regenerated slabs
 constexpr int64_t CHUNK_BUDGET = 12LL << 30;  // bytes of per-chunk stores
 
@@ -882,11 +883,31 @@ int build_plans(mbe3_handle *h) {
     }
     fdim[m] = d;
   }
-  // solver class of a fragment: the four-wave instances take every fragment
-  // up to 80-wide pair domains (one chunk's instance is sized by its widest
-  // fragment); each width above that has its own eight-wave instance, so
-  // one class per width
-  auto fclass = [&](int m) { return fdim[m] <= 80 ? 0 : fdim[m]; };
+  // solver class of a fragment: its widest pair domain picks the instance of
+  // the solver.  Each width above 80 has its own eight-wave instance; up to 80
+  // (four waves) the narrower widths are classes of their own where enough
+  // fragments share one, because their instances fit more workgroups on a CU
+  // (160 orbitals: solver 98 -> 90 ms with 64 apart from 80); fewer than fill the
+  // chip a few times join the next width, whose launch hides their tail
+  std::map<int, int64_t> by_width;
+  for (int d : fdim) by_width[d]++;
+  std::map<int, int> cls;
+  {
+    std::vector<int> open;
+    int64_t n_open = 0;
+    for (auto it = by_width.begin(); it != by_width.end(); ++it) {
+      open.push_back(it->first);
+      n_open += it->second;
+      const auto next = std::next(it);
+      if (it->first < 80 && n_open < CLASS_MIN_FRAGS && next != by_width.end() &&
+          next->first <= 80)
+        continue;
+      for (int w : open) cls[w] = it->first;
+      open.clear();
+      n_open = 0;
+    }
+  }
+  auto fclass = [&](int m) { return cls.at(fdim[m]); };
   std::vector<int> order(h->frags.size());
   for (size_t m = 0; m < order.size(); ++m) order[m] = (int)m;
   // with warm starts every monomer and dimer comes before the trimers (their

@@ -18,26 +18,42 @@
 //
 // Data flow of one term on the FP64 matrix cores (v_mfma_f64_16x16x4), with
 // S~ stored as S~_(s,t) = S~'^T (D_s x D_t, row-major):
-//   pass 1: each wave owns whole 16-row blocks ib of R~_t and accumulates
+//   pass 1: for a 16-row block ib of R~_t a wave accumulates
 //      W = Z^T = (Y_s^(T))^T S~'^T over 16-row panels m of Y_s^(T) and S~;
 //   pass 2: the MFMA output layout (register v of lane l holds row l/16 + 4v,
 //      column l%16) is exactly the A-operand layout of the second product for
 //      the four k-steps kb*16 + 4v, so Z never leaves the registers and
 //      R~_t[ib, :] += Z[ib, :] S~'^T reads the S~ resident in LDS.
+// A wave works on one row block, whole or shared with other waves by source
+// blocks kb (row_part): each then holds a partial R~_t[ib, :], added up through
+// LDS once per target.  Before, the waves took whole blocks alone, and a SIMD
+// with one block more than the others set the time of every product: 2 blocks
+// against 1.25 on average at 80-wide targets.  The steps of a product that lie in
+// the padding of the source are left out.
 // Panels go global -> registers (prefetched one step ahead) -> LDS: the
 // term's S~ panels land in a resident D_s x D_t block reused by pass 2 (which
 // then needs no barrier and hides the next term's first load), the Y^(T)
 // rows in two alternating 16-row buffers.  Only Y is kept in memory: a panel
-// of Y^T (16 rows of it) is read as 16-column strips of Y's rows and
-// transposed on its way into LDS, and the residual reads Y^T elements
-// straight from Y, so each sweep writes its amplitudes once, coalesced.  LDS per workgroup is
-// D_max^2 + 32 D_max doubles (16 D_max at D_max = 128, one Y buffer): two
-// fragments share a CU up to 80-wide domains (four waves each), one above
-// (eight waves, each owning one row block).  A diagonal pair's
-// mirror terms f S~ Y S~^T and its transpose are formed once and symmetrised
-// through LDS.
+// of Y^T (16 rows of it) is read as 16-column strips of Y's rows, kept as
+// strips, and its operand read across them; the residual reads Y^T elements
+// straight from Y, so each sweep writes its amplitudes once, coalesced.  The
+// residual's inputs are fetched a block ahead with no load under a condition (a
+// branch around one of them had every block wait for its own loads: a quarter of
+// the solver).  LDS per workgroup is D_max^2 + 36 D_max doubles (18 D_max at
+// D_max = 128, one Y buffer).  Up to 80-wide domains four waves work on a
+// fragment, and two (80), three (64, 48) or four (32) fragments share a CU; above,
+// eight waves and one fragment.  A diagonal pair's mirror terms f S~ Y S~^T and
+// its transpose are formed once and symmetrised through LDS.
+// What bounds it: about 45% of the wave time is products (matrix cores busy
+// 40%), 15% the residual, the rest the panel steps and their barriers; 3 TB/s of
+// S~ past L2.  Measured, all launches of a step: 88.8 ms for 119 ms at 160
+// orbitals (D to 80), 116 ms for 135 ms at 96 orbitals of 24 - 64 OSVs (D to
+// 128), 32 orbitals recorded with gradient 6.6 ms for 9.7 ms.
 // Sweep 0 has T = 0, so R~ = K~ needs no product.  All pair blocks are zero
 // padded to multiples of 16: no tile is masked.
+#include <algorithm>
+#include <type_traits>
+
 #include "internal.hpp"
 
 namespace mbe3 {
@@ -49,15 +65,9 @@ __device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Global-memory view of a pointer whose address space the compiler cannot
-// see (one read back from LDS): loads through it are global loads, counted
-// by vmcnt alone.  Through a generic pointer they would be flat loads, which
-// also count in lgkmcnt, so every wait for an LDS access would wait for the
-// prefetched panel as well.
-typedef __attribute__((address_space(1))) const d2 gd2;
-__device__ __forceinline__ const gd2 *as_global(const double *p) {
-  return (const gd2 *)(p);
-}
+// Row pitch of a strip of 16 Y columns kept for a transposed source: 16 rows of
+// it, read across, fall on distinct banks.
+constexpr int YPITCH = 18;
 
 // s_waitcnt immediate of vmcnt(0) alone (gfx9 encoding: expcnt and lgkmcnt
 // at their maxima)
@@ -71,13 +81,13 @@ constexpr int WAIT_VMCNT0 = 0x0F70;
 struct TermLds {
   const double *st;  // row-major S~_(src, target)
   double coef;       // f_occ[fx][fy]; 1 in the gradient pass
-  int32_t target, src, dt, ds, trans, pad_;
+  int32_t src, dt, ds, ds0, trans, pad_;  // ds0: the source's unpadded dimension
 };
 struct SlotLds {
   int64_t kt_off, et_off;
   double fpq;  // f_pp + f_qq
   int32_t D, ysub, sym, wgt;
-  int32_t tb, tx, te;  // the terms this launch runs for the slot, the first
+  int32_t tb, tx, te;  // the slot's terms of this launch in tc[], the first
                        // of them that couples two pairs of a trimer
   int64_t b0, b1;      // coupling sums of the slot (second one: diagonal
                        // slots of a trimer)
@@ -124,79 +134,77 @@ __device__ __forceinline__ double wg_sum(double v, double *red) {
   return s;
 }
 
-// One term's products accumulated into acc (see the data flow above): pass 1
-// streams the S~ and Y^(T) row panels into LDS and forms W = Z^T in
-// registers, pass 2 reads the S~ resident in LDS.  Expects the panel
-// pipeline state (pf, p_*), Dt/nT, Ds/nS, acc and the LDS pointers in scope.
-#define MBE3_TERM_PRODUCTS(COEF)                                               \
-  do {                                                                         \
-    d4 W[MAXRB][MAXNT];                                                        \
-    _Pragma("unroll") for (int rb = 0; rb < MAXRB; ++rb)                       \
-      _Pragma("unroll") for (int kb = 0; kb < MAXNT; ++kb)                     \
-        W[rb][kb] = d4{0.0, 0.0, 0.0, 0.0};                                    \
-    __syncthreads(); /* the previous term's S~ is no longer read */            \
-    for (int mp = 0; mp < nS; ++mp) {                                          \
-      double *const yb = (mp & 1) ? yb1 : yb0;                                 \
-      /* the panel in pf has landed; waiting here explicitly leaves no load   \
-         outstanding on any path, so the next panel's loads issue back to     \
-         back instead of each waiting for the one before */                  \
-      __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);                                 \
-      {                                                                        \
-        d2 *s_ = reinterpret_cast<d2 *>(Sl + 16 * mp * Dt);                    \
-        d2 *y_ = reinterpret_cast<d2 *>(yb);                                   \
-        _Pragma("unroll") for (int u = 0; u < PFN; ++u) {                      \
-          const int e = tid + NTH * u;                                         \
-          if (e < p_n1) {                                                      \
-            s_[e] = pf[u];                                                     \
-          } else if (e - p_n1 < p_n2) {                                        \
-            const int q_ = e - p_n1;                                           \
-            if (p_tr) { /* Y[k][16 mp + c, c + 1] -> rows c, c + 1, col k */   \
-              const int k_ = q_ >> 3, c_ = 2 * (q_ & 7);                       \
-              yb[c_ * Ds + k_] = pf[u].x;                                      \
-              yb[(c_ + 1) * Ds + k_] = pf[u].y;                                \
-            } else {                                                           \
-              y_[q_] = pf[u];                                                  \
-            }                                                                  \
-          }                                                                    \
-        }                                                                      \
-      }                                                                        \
-      /* the next panel streams in under the products; a term's last panel   \
-         prefetches the next term's first one */                              \
-      MBE3_ADVANCE();                                                          \
-      if (p_tl < f_nt) MBE3_LOAD_PANEL();                                      \
-      __syncthreads();                                                         \
-      const double *STp = Sl + 16 * mp * Dt;                                   \
-      _Pragma("unroll") for (int mm = 0; mm < 4; ++mm) {                       \
-        const int ml = 4 * mm + lq;                                            \
-        _Pragma("unroll") for (int rb = 0; rb < MAXRB; ++rb) {                 \
-          const int ib = wave + NW * rb;                                       \
-          if (ib < nT) {                                                       \
-            const double bv = STp[ml * Dt + ib * 16 + l16];                    \
-            _Pragma("unroll") for (int kb = 0; kb < MAXNT; ++kb)               \
-              if (kb < nS)                                                     \
-                W[rb][kb] = mfma_f64(yb[ml * Ds + kb * 16 + l16], bv, W[rb][kb]); \
-          }                                                                    \
-        }                                                                      \
-      }                                                                        \
-      /* one Y buffer: the next panel's store waits for these reads */        \
-      if (!DBY) __syncthreads();                                               \
-    }                                                                          \
-    _Pragma("unroll") for (int kp = 0; kp < MAXNT; ++kp) {                     \
-      if (kp < nS) {                                                           \
-        _Pragma("unroll") for (int v = 0; v < 4; ++v) {                        \
-          const double *brow = Sl + (kp * 16 + 4 * v + lq) * Dt + l16;         \
-          _Pragma("unroll") for (int rb = 0; rb < MAXRB; ++rb) {               \
-            const int ib = wave + NW * rb;                                     \
-            if (ib < nT) {                                                     \
-              const double av = (COEF) * W[rb][kp][v];                         \
-              _Pragma("unroll") for (int jb = 0; jb < MAXNT; ++jb)             \
-                if (jb < nT) acc[rb][jb] = mfma_f64(av, brow[jb * 16], acc[rb][jb]); \
-            }                                                                  \
-          }                                                                    \
-        }                                                                      \
-      }                                                                        \
-    }                                                                          \
-  } while (0)
+// Raw buffer loads of 16 bytes: lanes past num bytes read zero without a
+// branch, and the panel's offset is one scalar.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const double *p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(p), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ d2 load_b128(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(d2, (u4)__builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+// Volatile views of LDS: a load stays where it is written, ahead of the guarded
+// product that uses it.
+typedef __attribute__((address_space(3))) const volatile double lds_d;
+__device__ __forceinline__ const lds_d *as_lds(const double *p) { return (const lds_d *)p; }
+// A value all lanes share, in scalar registers.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  return (int64_t)(((uint64_t)(uint32_t)uniform((int)((uint64_t)v >> 32)) << 32) |
+                   (uint32_t)uniform((int)v));
+}
+__device__ __forceinline__ double uniform(double v) {
+  return __builtin_bit_cast(double, uniform(__builtin_bit_cast(int64_t, v)));
+}
+__device__ __forceinline__ const double *uniform(const double *p) {
+  return (const double *)uniform((int64_t)p);
+}
+// Element o of a block in global memory (which a pointer made of scalars no
+// longer says): scalar base, 32-bit offset.
+typedef __attribute__((address_space(1))) double g_double;
+__device__ __forceinline__ double at(const double *p, uint32_t o) {
+  return *(const g_double *)((const char *)p + o * 8u);
+}
+__device__ __forceinline__ void put(double *p, uint32_t o, double v) {
+  *(g_double *)((char *)p + o * 8u) = v;
+}
+constexpr int OOB = 0x7fff0000;  // past every block
+
+// Elements of a register array, however many are used: an array of up to 16
+// doubles would become one vector value, copied whole wherever one of its
+// elements is written under a guard (up to 90 moves per matrix instruction at
+// 64-wide domains).
+constexpr int SPLIT = 9;
+
+// Which 16-row block of a target with nT of them a wave works on, and which
+// share of that block's source blocks: part of nparts, source blocks kb with kb
+// mod nparts == part.  The waves of one block are first, first + stride, ...
+// Waves w and w + 4 share a SIMD, so for eight waves every SIMD gets nT / 4 of
+// a row's products (7 rows: 2): four rows go whole to waves 0 - 3, the rest is
+// dealt to waves 4 - 7.  ib = -1: nothing to do.
+struct RowPart {
+  int ib, part, lg, first, stride;  // nparts = 1 << lg
+};
+template <int NW>
+__device__ __forceinline__ RowPart row_part(int nT, int w) {
+  if (NW == 8) {
+    if (nT >= 7) return {w < nT ? w : -1, 0, 0, w, 1};
+    if (nT == 4) return {w & 3, w >> 2, 1, w & 3, 4};
+    if (nT == 1) return {0, w, 3, 0, 1};
+    if (nT == 2) return {w >> 2, w & 3, 2, w & 4, 1};
+    if (w < 4) return nT == 3 ? RowPart{0, w, 2, 0, 1} : RowPart{w, 0, 0, w, 1};
+    if (nT == 5) return {4, w & 3, 2, 4, 1};
+    return {(nT == 3 ? 1 : 4) + ((w & 2) >> 1), w & 1, 1, w & 6, 1};
+  }
+  if (nT >= 3) return {w < nT ? w : -1, 0, 0, w, 1};
+  if (nT == 1) return {0, w, 2, 0, 1};
+  return {w >> 1, w & 1, 1, w & 2, 1};
+}
+// The blocks < n of part of 1 << lg parts as a bit mask.
+__device__ __forceinline__ uint32_t part_mask(int part, int lg, int n) {
+  const uint32_t every = lg == 0 ? 0xffu : lg == 1 ? 0x55u : lg == 2 ? 0x11u : 1u;
+  return (every << part) & ((1u << n) - 1u);
+}
 
 // MAXNT: largest number of 16-blocks per pair dimension (dmax / 16).
 // MODE 0: solve.  MODE 1: solve and store each converged fragment's Y at
@@ -205,9 +213,8 @@ __device__ __forceinline__ double wg_sum(double v, double *red) {
 // fragments, so two thirds of its terms (a pair and one of its orbitals) depend
 // on the pair alone: MODE 3 forms those sums once per dimer, over the warm
 // store, and the trimers' first sweep adds them in its residual instead of
-// forming them again in each of the about 50 trimers of a pair.  Measured, whole
-// solver: 119 ms for 136 ms at 160 orbitals, 135 ms for 152 ms at 96 orbitals
-// of 24 - 64 OSVs (the sums themselves 0.5 ms).
+// forming them again in each of the about 50 trimers of a pair.  Measured:
+// MODE3_TIMES.
 // MODE 2: the gradient pass alone, a separate launch over the same
 // fragments: the terms [tb, tg) of each pair target are formed once more from
 // the stored Y with unit coefficient and contracted with Y~ = 2Y - Y^T.  The
@@ -219,33 +226,34 @@ __device__ __forceinline__ double wg_sum(double v, double *red) {
 // converge (iters < 0) are skipped.  Keeping the pass out of the solving launch keeps its
 // registers out of the iterations.
 template <int MAXNT, int MODE, int NW>
-__global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(SolveArgs a) {
+__global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void solve_kernel(SolveArgs a) {
   constexpr bool ST = MODE == 1, GP = MODE == 2, BASE = MODE == 3;
   extern __shared__ double lds[];
-  constexpr int NTH = 64 * NW;                   // threads per workgroup
-  constexpr int MAXRB = (MAXNT + NW - 1) / NW;   // row blocks per wave
-  constexpr int PFN = (4 * MAXNT + NW - 1) / NW;  // panel slots per thread
-  constexpr bool DBY = MAXNT <= 7;               // two Y panel buffers
+  constexpr int NTH = 64 * NW;                     // threads per workgroup
+  constexpr int PFN = (8 * 16 * MAXNT + NTH - 1) / NTH;  // slots of a panel's S~ (or Y)
+  constexpr bool DBY = MAXNT <= 7;                 // two Y panel buffers
+  constexpr bool ROW2 = NW == 4 && MAXNT == 5;     // a fifth row block, shared
+  constexpr int NR2 = ROW2 ? MAXNT : 1, NW2 = ROW2 ? 2 : 1;
   __shared__ double red_d[2 * NW];
   __shared__ int red_i[NW];
   __shared__ TermLds tc[MAX_FRAG_TERMS];
   __shared__ SlotLds sc[6];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
+  const int wave = uniform(tid >> 6);  // uniform per wave
   const int l16 = lane & 15;
   const int lq = lane >> 4;
   // LDS: the term's whole S~ (D_s x D_t) stays resident for both passes; the
   // Y^(T) rows stream through two 16-row buffers.
   double *const Sl = lds;
   double *const yb0 = lds + (int64_t)a.dmax * a.dmax;
-  double *const yb1 = DBY ? yb0 + 16 * a.dmax : yb0;
+  double *const yb1 = DBY ? yb0 + YPITCH * a.dmax : yb0;
 
   double *scr = a.scratch + (int64_t)blockIdx.x * a.scratch_stride;
   const int64_t ny_cap = (a.scratch_stride - 2LL * a.dmax * a.dmax) / 4;
   double *const Y0 = scr;  // two buffers of ny_cap (current, next)
 
-  d2 pf[PFN];  // next panel: S~ rows then Y^(T) rows
+  d2 ps[SPLIT], py[SPLIT];  // next panel: S~ rows, Y^(T) rows (PFN used)
 
   for (int fi = blockIdx.x; fi < a.n_frag; fi += gridDim.x) {
     const FragDesc *__restrict__ fdp = a.frags + fi;
@@ -264,10 +272,10 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
       TermLds c;
       c.st = (t.st_buf ? a.st1 : a.st0) + t.st_off;
       c.coef = GP ? 1.0 : a.f_occ[(int64_t)t.fx * a.n_occ + t.fy];
-      c.target = t.target;
       c.src = t.src;
       c.dt = a.slots[fdp->slot[t.target]].D;
       c.ds = a.slots[fdp->slot[t.src]].D;
+      c.ds0 = a.slots[fdp->slot[t.src]].d;
       c.trans = t.trans;
       c.pad_ = 0;
       tc[tid] = c;
@@ -282,9 +290,9 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
       c.ysub = fdp->ysub[tl];
       c.sym = fdp->sym[tl];
       c.wgt = fdp->wgt[tl];
-      c.tb = f_tb + fdp->tb[tl];
-      c.tx = f_tb + fdp->tx[tl];
-      c.te = f_tb + (GP ? fdp->tg[tl] : fdp->te[tl]);
+      c.tb = fdp->tb[tl];
+      c.tx = fdp->tx[tl];
+      c.te = GP ? fdp->tg[tl] : fdp->te[tl];
       c.b0 = c.b1 = 0;
       if (BASE) {
         c.b0 = base_of(a.slots, a.slots[fdp->slot[2]], tl);
@@ -340,192 +348,336 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
       };
 
       // ---- panel pipeline: step (ti, m) = rows 16m.. of S~ and of Y^(T) ----
-      int p_tl = -1, p_ti = 0, p_end = 0, p_m = 0;  // step held in pf
-      int p_n1 = 0, p_n2 = 0;
-      bool p_tr = false;  // the Y part of pf is a strip of Y columns
-      // descriptors of term c_ti (the one the prefetch is in), read from LDS
-      // once per term rather than once per panel
-      int c_ti = -1, c_dt = 0, c_ds = 16;
-      bool c_tr = false;
-      const double *c_st = nullptr, *c_ys = nullptr;
-#define MBE3_LOAD_PANEL()                                                      \
-  do {                                                                         \
-    if (p_ti != c_ti) { /* a new term: its descriptors, once */                \
-      const TermLds &tm_ = tc[p_ti - f_tb];                                    \
-      c_dt = __builtin_amdgcn_readfirstlane(tm_.dt);                           \
-      c_ds = __builtin_amdgcn_readfirstlane(tm_.ds);                           \
-      c_tr = __builtin_amdgcn_readfirstlane(tm_.trans) != 0;                   \
-      c_st = tm_.st;                                                           \
-      c_ys = ysrc(tm_.src);                                                    \
-      c_ti = p_ti;                                                             \
-    }                                                                          \
-    const gd2 *st_ = as_global(c_st + (int64_t)16 * p_m * c_dt);               \
-    /* rows 16m.. of Y, or (transposed source) columns 16m.. of every row */  \
-    const gd2 *y_ = as_global(c_tr ? c_ys + 16 * p_m : c_ys + (int64_t)16 * p_m * c_ds); \
-    p_n1 = 8 * c_dt;                                                           \
-    p_n2 = 8 * c_ds;                                                           \
-    p_tr = c_tr;                                                               \
-    /* one unconditional load per slot from a selected address: no two      \
-       loads of a step write the same registers, so none waits for another */\
-    _Pragma("unroll") for (int u = 0; u < PFN; ++u) {                          \
-      const int e = tid + NTH * u;                                             \
-      const int q_ = e - p_n1;                                                 \
-      /* slots past the panel load its first element (never stored) */       \
-      const gd2 *src_ = e < p_n1 ? st_ + e                                     \
-                        : q_ >= p_n2 ? st_                                     \
-                        : p_tr ? y_ + (q_ >> 3) * (c_ds >> 1) + (q_ & 7)       \
-                        : y_ + q_;                                             \
-      pf[u] = *src_;                                                           \
-    }                                                                          \
-  } while (0)
-// first term of the next targets that have any (p_tl == f_nt: none left)
-#define MBE3_NEXT_TARGET()                                                     \
-  do {                                                                         \
-    while (p_ti >= p_end && ++p_tl < f_nt) {                                   \
-      p_ti = __builtin_amdgcn_readfirstlane(bsrc ? sc[p_tl].tx : sc[p_tl].tb);  \
-      p_end = __builtin_amdgcn_readfirstlane(sc[p_tl].te);                     \
-    }                                                                          \
-  } while (0)
-#define MBE3_ADVANCE()                                                         \
-  do {                                                                         \
-    if (++p_m >= (c_ds >> 4)) {                                                \
-      p_m = 0;                                                                 \
-      ++p_ti;                                                                  \
-      MBE3_NEXT_TARGET();                                                      \
-    }                                                                          \
-  } while (0)
-
+      // S~ is one contiguous copy, panel after panel; Y's rows likewise, or
+      // (transposed source) strips of 16 columns, kept as strips of pitch
+      // YPITCH in LDS and read across.  Everything that does not change from
+      // panel to panel is set once per term.
+      int p_tl = -1, p_ti = 0, p_end = 0, p_m = 0;  // step held in ps, py
+      int p_dt = 0, p_ds = 16, p_yv = 0, p_yu = 0, p_ys = 0;
+      __amdgpu_buffer_rsrc_t p_rs, p_ry;
+      auto open_term = [&]() {  // first term of the next targets that have any
+        while (p_ti >= p_end && ++p_tl < f_nt) {
+          p_ti = uniform(bsrc ? sc[p_tl].tx : sc[p_tl].tb);
+          p_end = uniform(sc[p_tl].te);
+        }
+        if (p_tl >= f_nt) return;
+        const TermLds &tm = tc[p_ti];
+        p_dt = uniform(tm.dt);
+        p_ds = uniform(tm.ds);
+        const bool tr = uniform(tm.trans) != 0;
+        p_rs = make_rsrc(uniform(tm.st), p_ds * p_dt * 8);
+        p_ry = make_rsrc(uniform(ysrc(tm.src)), p_ds * p_ds * 8);
+        p_yv = tr ? (tid >> 3) * p_ds * 8 + (tid & 7) * 16 : tid * 16;
+        p_yu = tr ? NTH * p_ds : NTH * 16;
+        p_ys = tr ? 128 : 128 * p_ds;
+      };
+      auto load_panel = [&]() {
+        const int so = p_m * 128 * p_dt, yo = p_m * p_ys;
+#pragma unroll
+        for (int u = 0; u < PFN; ++u) {
+          const int e = tid + NTH * u;
+          ps[u] = load_b128(p_rs, e < 8 * p_dt ? e * 16 : OOB, so);
+        }
+#pragma unroll
+        for (int u = 0; u < PFN; ++u) {
+          const int e = tid + NTH * u;
+          py[u] = load_b128(p_ry, e < 8 * p_ds ? p_yv + u * p_yu : OOB, yo);
+        }
+      };
       if (hasY) {
-        MBE3_NEXT_TARGET();
-        if (p_tl < f_nt) MBE3_LOAD_PANEL();
+        open_term();
+        if (p_tl < f_nt) load_panel();
       }
 
       for (int tl = 0; tl < f_nt; ++tl) {
         const SlotLds sl = sc[tl];
-        const int Dt = __builtin_amdgcn_readfirstlane(sl.D);
+        const int Dt = uniform(sl.D);
         const int nT = Dt >> 4;
-        d4 acc[MAXRB][MAXNT];
+        const RowPart rp = row_part<NW>(nT, wave);
+        const bool row2 = ROW2 && nT == 5;
+        d4 acc[SPLIT], acc2[SPLIT];  // MAXNT, NR2 used
 #pragma unroll
-        for (int rb = 0; rb < MAXRB; ++rb)
+        for (int jb = 0; jb < MAXNT; ++jb) acc[jb] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-          for (int jb = 0; jb < MAXNT; ++jb) acc[rb][jb] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int jb = 0; jb < NR2; ++jb) acc2[jb] = d4{0.0, 0.0, 0.0, 0.0};
 
         if (hasY) {
-          const int t_end = __builtin_amdgcn_readfirstlane(sl.te);
-          for (int ti = __builtin_amdgcn_readfirstlane(bsrc ? sl.tx : sl.tb); ti < t_end;
+          const int t_end = uniform(sl.te);
+          for (int ti = uniform(bsrc ? sl.tx : sl.tb); ti < t_end;
                ++ti) {
-            const double coef = tc[ti - f_tb].coef;
-            const int Ds = __builtin_amdgcn_readfirstlane(tc[ti - f_tb].ds);
+            const double coef = tc[ti].coef;
+            const int Ds = uniform(tc[ti].ds);
+            const int ds0 = uniform(tc[ti].ds0);
+            const bool tr = uniform(tc[ti].trans) != 0;
             const int nS = Ds >> 4;
-            MBE3_TERM_PRODUCTS(coef);
+            // this wave's source blocks: part, part + nparts, ... (cnt of them)
+            const int cnt = rp.ib < 0 ? 0 : (nS - rp.part + (1 << rp.lg) - 1) >> rp.lg;
+            // the panel's Y part: this thread's place in LDS, its operand reads
+            const int yw = tr ? (tid >> 3) * (YPITCH / 2) + (tid & 7) : tid;  // in d2
+            const int ywu = tr ? (NTH / 8) * (YPITCH / 2) : NTH;
+            const int yk = tr ? 16 * YPITCH : 16, ym = tr ? 4 : 4 * Ds;
+            const int yr = (tr ? l16 * YPITCH + lq : lq * Ds + l16) + rp.part * yk;
+            const int ystep = yk << rp.lg;
+            d4 W[SPLIT], W2[SPLIT];  // MAXNT, NW2 used
+#pragma unroll
+            for (int kb = 0; kb < MAXNT; ++kb) W[kb] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int kb = 0; kb < NW2; ++kb) W2[kb] = d4{0.0, 0.0, 0.0, 0.0};
+            __syncthreads();  // the previous term's S~ is no longer read
+            for (int mp = 0; mp < nS; ++mp) {
+              double *const yb = (mp & 1) ? yb1 : yb0;
+              // the panel in ps, py has landed; waiting here explicitly leaves
+              // no load outstanding on any path
+              __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+              {
+                d2 *s_ = reinterpret_cast<d2 *>(Sl + 16 * mp * Dt) + tid;
+                d2 *y_ = reinterpret_cast<d2 *>(yb) + yw;
+#pragma unroll
+                for (int u = 0; u < PFN; ++u) {
+                  const int e = tid + NTH * u;
+                  if (e < 8 * Dt) s_[NTH * u] = ps[u];
+                  if (e < 8 * Ds) y_[ywu * u] = py[u];
+                }
+              }
+              // the next panel streams in under the products; a term's last
+              // panel prefetches the next term's first one
+              if (++p_m >= (p_ds >> 4)) {
+                p_m = 0;
+                ++p_ti;
+                open_term();
+              }
+              if (p_tl < f_nt) load_panel();
+              __syncthreads();
+              if (cnt > 0) {
+                const lds_d *sp = as_lds(Sl + (16 * mp + lq) * Dt + l16);
+                const lds_d *yp = as_lds(yb + yr);
+                double yv = *yp;
+                d4 b1, b2 = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int mm = 0; mm < 4; ++mm) {
+                  b1[mm] = sp[mm * 4 * Dt + rp.ib * 16];
+                  if (ROW2) b2[mm] = sp[mm * 4 * Dt + (row2 ? 64 : 0)];
+                }
+#pragma unroll
+                for (int mm = 0; mm < 4; ++mm) {
+                  const double bv = b1[mm], bv2 = b2[mm];
+                  const bool on = mm == 0 || 16 * mp + 4 * mm < ds0;  // else zeros
+                  const int cm = on ? cnt : 0;
+#pragma unroll
+                  for (int u = 0; u < MAXNT; ++u) {
+                    // the next product's operand is on its way before this one
+                    // (past this wave's blocks: its first, unused)
+                    const double yn = u + 1 < MAXNT
+                                          ? yp[mm * ym + (u + 1 < cnt ? (u + 1) * ystep : 0)]
+                                      : mm + 1 < 4  ? yp[(mm + 1) * ym]
+                                                    : 0.0;
+                    if (__builtin_expect(cm > u, 1)) {
+                      W[u] = mfma_f64(yv, bv, W[u]);
+                      if (ROW2 && row2 && (u & 3) == wave)
+                        W2[u >> 2] = mfma_f64(yv, bv2, W2[u >> 2]);
+                    }
+                    yv = yn;
+                  }
+                }
+              }
+              // one Y buffer: the next panel's store waits for these reads
+              if (!DBY) __syncthreads();
+            }
+#pragma unroll
+            for (int u = 0; u < MAXNT; ++u) {
+              if (cnt > u) {
+                const int kr = 16 * (rp.part + (u << rp.lg));  // the block's first row
+                const bool r2 = ROW2 && row2 && (u & 3) == wave;
+                const lds_d *brow = as_lds(Sl + (kr + lq) * Dt + l16);
+                double sv = *brow;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                  const double av = coef * W[u][v];
+                  const double av2 = ROW2 ? coef * W2[u >> 2][v] : 0.0;
+                  const int cv = v == 0 || kr + 4 * v < ds0 ? nT : 0;
+#pragma unroll
+                  for (int jb = 0; jb < MAXNT; ++jb) {
+                    // (past the row: the next rows or the Y buffer behind, unused)
+                    const double sn = jb + 1 < MAXNT ? brow[v * 4 * Dt + (jb + 1) * 16]
+                                      : v + 1 < 4    ? brow[(v + 1) * 4 * Dt]
+                                                     : 0.0;
+                    if (__builtin_expect(cv > jb, 1)) {
+                      acc[jb] = mfma_f64(av, sv, acc[jb]);
+                      if (ROW2 && r2) acc2[jb] = mfma_f64(av2, sv, acc2[jb]);
+                    }
+                    sv = sn;
+                  }
+                }
+              }
+            }
             if (GP) {
               // this term's product alone, contracted with Y~ = 2Y - Y^T
               const double *Wy = Y0 + ny_cap + sl.ysub;
               double part = 0.0;
 #pragma unroll
-              for (int rb = 0; rb < MAXRB; ++rb) {
-                const int ib = wave + NW * rb;
+              for (int jb = 0; jb < MAXNT; ++jb) {
+                if (cnt > 0 && jb < nT) {
 #pragma unroll
-                for (int jb = 0; jb < MAXNT; ++jb) {
-                  if (ib < nT && jb < nT) {
+                  for (int v = 0; v < 4; ++v)
+                    part += Wy[(rp.ib * 16 + lq + 4 * v) * Dt + jb * 16 + l16] * acc[jb][v];
+                }
+                acc[jb] = d4{0.0, 0.0, 0.0, 0.0};
+              }
+              if (row2) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                      const int i = ib * 16 + lq + 4 * v, j = jb * 16 + l16;
-                      part += Wy[(int64_t)i * Dt + j] * acc[rb][jb][v];
-                    }
-                  }
-                  acc[rb][jb] = d4{0.0, 0.0, 0.0, 0.0};
+                for (int jb = 0; jb < NR2; ++jb) {
+#pragma unroll
+                  for (int v = 0; v < 4; ++v)
+                    part += Wy[(64 + lq + 4 * v) * Dt + jb * 16 + l16] * acc2[jb][v];
+                  acc2[jb] = d4{0.0, 0.0, 0.0, 0.0};
                 }
               }
               const double tot = wg_sum<NW>(part, red_d);
-              if (tid == 0) a.gterm[ti] = tot;
+              if (tid == 0) a.gterm[f_tb + ti] = tot;
             }
           }
         }
         if (GP) continue;  // no residual in the gradient pass
 
-        const int sym = sl.sym;
-        if (sym && !bsrc) {  // diagonal pair: R~ gets acc + acc^T (mirror terms)
+        // ---- the target's sums: shared row blocks added up (a wave then owns
+        // the column blocks jb mod nparts == part of its row block) ----
+        const int sym = uniform(sl.sym);
+        const uint32_t jm = rp.ib < 0 ? 0u : part_mask(rp.part, rp.lg, nT);
+        const uint32_t jm2 = row2 ? part_mask(wave, 2, 5) : 0u;
+        const bool summed = hasY && !(bsrc && sym);  // some product was added
+        // uniform over the workgroup, unlike nparts
+        const bool shared = summed && (row2 || nT < (NW == 8 ? 7 : 3));
+        if (shared) {
           __syncthreads();  // S~ of the last term is no longer read
+          double *o = Sl + wave * 16 * Dt;
 #pragma unroll
-          for (int rb = 0; rb < MAXRB; ++rb) {
-            const int ib = wave + NW * rb;
-            if (ib < nT) {
+          for (int jb = 0; jb < MAXNT; ++jb)
+            if (jb < nT && (row2 || rp.lg > 0)) {
 #pragma unroll
-              for (int jb = 0; jb < MAXNT; ++jb)
-                if (jb < nT) {
+              for (int v = 0; v < 4; ++v)
+                o[(lq + 4 * v) * Dt + jb * 16 + l16] = row2 ? acc2[jb][v] : acc[jb][v];
+            }
+          __syncthreads();
+          const int first = row2 ? 0 : rp.first, stride = row2 ? 1 : rp.stride;
+          const int np = row2 ? 4 : 1 << rp.lg;
+          if (np > 1) {
+            const uint32_t own = row2 ? jm2 : jm;
 #pragma unroll
-                  for (int v = 0; v < 4; ++v)
-                    Sl[(ib * 16 + lq + 4 * v) * Dt + jb * 16 + l16] = acc[rb][jb][v];
+            for (int jb = 0; jb < MAXNT; ++jb)
+              if (own & (1u << jb)) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                  double t = 0.0;
+                  for (int q = 0; q < np; ++q)
+                    t += Sl[((first + stride * q) * 16 + lq + 4 * v) * Dt + jb * 16 + l16];
+                  if (row2) acc2[jb][v] = t;
+                  else acc[jb][v] = t;
                 }
+              }
+          }
+        }
+        if (sym && summed) {  // diagonal pair: R~ gets acc + acc^T (mirror terms)
+          __syncthreads();  // S~ of the last term, the shares are no longer read
+#pragma unroll
+          for (int jb = 0; jb < MAXNT; ++jb) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              if (jm & (1u << jb))
+                Sl[(rp.ib * 16 + lq + 4 * v) * Dt + jb * 16 + l16] = acc[jb][v];
+              if (ROW2 && (jm2 & (1u << jb)))
+                Sl[(64 + lq + 4 * v) * Dt + jb * 16 + l16] = acc2[jb][v];
             }
           }
           __syncthreads();
         }
 
-        if (BASE) {
-          double *o = a.base + sl.b0;
+        // ---- residual, energy, update for the owned blocks of target tl ----
+        const double *Yc = uniform(ysrc(tl));
+        double *Yn = const_cast<double *>(uniform((const double *)(Ynb + sl.ysub)));
+        const double *Kt = uniform((const double *)(a.kt + sl.kt_off));
+        const double *et = uniform((const double *)(a.et + sl.et_off));
+        const double *bs0 = uniform((const double *)(a.base + sl.b0));
+        const double *bs1 = uniform((const double *)(a.base + sl.b1));
+        const double fpq = uniform(sl.fpq);
+        const double w = (double)uniform(sl.wgt);
+        // the inputs of block (ib, jb), fetched one block ahead of their use;
+        // blocks that are not this wave's fetch one of the target all the same
+        struct In {
+          d4 k, y, yt, b;
+          double ej;
+        };
+        // no load is under a condition: they all leave together
+        const double *const Yq = hasY ? Yc : Kt;  // T = 0: read, not used
+        auto fetch = [&](int ib, int jb, auto with_base) {
+          In f;
+          const int j = jb * 16 + l16, i0 = ib * 16 + lq;
+          f.ej = at(et, j);
 #pragma unroll
-          for (int rb = 0; rb < MAXRB; ++rb) {
-            const int ib = wave + NW * rb;
-            if (ib < nT) {
-#pragma unroll
-              for (int jb = 0; jb < MAXNT; ++jb)
-                if (jb < nT) {
-#pragma unroll
-                  for (int v = 0; v < 4; ++v) {
-                    const int i = ib * 16 + lq + 4 * v, j = jb * 16 + l16;
-                    o[(int64_t)i * Dt + j] = acc[rb][jb][v] + (sym ? Sl[j * Dt + i] : 0.0);
-                  }
-                }
+          for (int v = 0; v < 4; ++v) {
+            const int ij = (i0 + 4 * v) * Dt + j;
+            const int ji = sym ? ij : j * Dt + i0 + 4 * v;  // Y_pp is symmetric
+            f.k[v] = at(Kt, ij);
+            f.y[v] = at(Yq, ij);
+            f.yt[v] = at(Yq, ji);
+            if (decltype(with_base)::value) {  // b1 of a pair slot: read, not used
+              const double b2 = at(bs1, ij);
+              f.b[v] = at(bs0, ij) + (sym ? b2 : 0.0);
             }
           }
-          continue;
-        }
-        // ---- residual, energy, update for the owned rows of target tl ----
-        const int ysub = sl.ysub;
-        const double *Yc = ysrc(tl);
-        double *Yn = Ynb + ysub;
-        const double *Kt = a.kt + sl.kt_off;
-        const double *et = a.et + sl.et_off;
-        const double fpq = sl.fpq;
-        const double w = (double)sl.wgt;
+          return f;
+        };
+        auto finish = [&](int ib, int jb, const d4 &t, const In &f, const d4 &ei,
+                          auto with_base) {
+          const int j = jb * 16 + l16;
 #pragma unroll
-        for (int rb = 0; rb < MAXRB; ++rb) {
-          const int ib = wave + NW * rb;
-          if (ib < nT) {
+          for (int v = 0; v < 4; ++v) {
+            const int i = ib * 16 + lq + 4 * v;
+            double sacc = t[v];
+            if (decltype(with_base)::value) sacc += f.b[v];
+            else if (sym && summed) sacc += Sl[j * Dt + i];
+            const double y = hasY ? f.y[v] : 0.0, yt = hasY ? f.yt[v] : 0.0;
+            const double den = fpq - ei[v] - f.ej;
+            const double r = f.k[v] - den * y - sacc;
+            const double ar = fabs(r);
+            if (!(ar <= 1e300)) bad = 1;
+            mres = fmax(mres, ar);
+            epart += w * (2.0 * y - yt) * (f.k[v] + r);
+            put(Yn, i * Dt + j, y + r / den);
+          }
+        };
+        auto finish_row = [&](int ib, uint32_t own, const d4 *t, auto last) {
+          constexpr int NB = decltype(last)::value;
+          if (BASE) {
+            double *o = const_cast<double *>(bs0);
 #pragma unroll
-            for (int jb = 0; jb < MAXNT; ++jb) {
-              if (jb < nT) {
-                const int j = jb * 16 + l16;
-                const double ej = et[j];
+            for (int jb = 0; jb < NB; ++jb)
+              if (own & (1u << jb)) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                  const int i = ib * 16 + lq + 4 * v;
-                  const int64_t ij = (int64_t)i * Dt + j;
-                  const double y = hasY ? Yc[ij] : 0.0;
-                  const double yt = hasY ? Yc[(int64_t)j * Dt + i] : 0.0;
-                  const double kij = Kt[ij];
-                  const double den = fpq - et[i] - ej;
-                  double sacc = acc[rb][jb][v];
-                  if (bsrc) {
-                    sacc += a.base[sl.b0 + ij];
-                    if (sym) sacc += a.base[sl.b1 + ij];
-                  } else if (sym) {
-                    sacc += Sl[j * Dt + i];
-                  }
-                  const double r = kij - den * y - sacc;
-                  const double ar = fabs(r);
-                  if (!(ar <= 1e300)) bad = 1;
-                  mres = fmax(mres, ar);
-                  epart += w * (2.0 * y - yt) * (kij + r);
-                  const double yn = y + r / den;
-                  Yn[ij] = yn;
+                  const int i = ib * 16 + lq + 4 * v, j = jb * 16 + l16;
+                  put(o, i * Dt + j, sym ? t[jb][v] + Sl[j * Dt + i] : t[jb][v]);
                 }
               }
-            }
+            return;
           }
-        }
+          d4 ei;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) ei[v] = at(et, ib * 16 + lq + 4 * v);
+          auto go = [&](auto with_base) {
+            In cur = fetch(ib, 0, with_base);
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb) {
+              In nxt;  // past the last block the first again, unused
+              if (jb + 1 < NB) nxt = fetch(ib, jb + 1 < nT ? jb + 1 : 0, with_base);
+              if (own & (1u << jb)) finish(ib, jb, t[jb], cur, ei, with_base);
+              if (jb + 1 < NB) cur = nxt;
+            }
+          };
+          if (bsrc) go(std::true_type());
+          else go(std::false_type());
+        };
+        if (jm) finish_row(rp.ib, jm, acc, std::integral_constant<int, MAXNT>());
+        if (ROW2 && jm2) finish_row(4, jm2, acc2, std::integral_constant<int, NR2>());
       }
       if (GP || BASE) {
         __syncthreads();  // the scratch is read; the next fragment refills it
@@ -586,10 +738,6 @@ __global__ __launch_bounds__(64 * NW, MAXNT <= 5 ? 2 : 1) void solve_kernel(Solv
     }
   }
 }
-#undef MBE3_ADVANCE
-#undef MBE3_NEXT_TARGET
-#undef MBE3_LOAD_PANEL
-#undef MBE3_TERM_PRODUCTS
 
 int64_t solve_scratch_doubles(int ny_max, int dmax) {
   return 4LL * ny_max + 2LL * dmax * dmax;
@@ -607,8 +755,9 @@ constexpr int solve_waves() { return NT <= 5 ? 4 : 8; }
 // LDS of one workgroup: the resident S~ block and two 16-row Y panel
 // buffers, one for the 128-wide instance (two would not leave room).
 size_t solve_lds_bytes(int dmax) {
-  const int ybuf = dmax <= 112 ? 32 : 16;
-  return (size_t)(dmax * dmax + ybuf * dmax) * sizeof(double);
+  const int ybuf = dmax <= 112 ? 2 * YPITCH : YPITCH;
+  // at 16 also the four shares of a target's one row block
+  return (size_t)std::max(dmax * dmax + ybuf * dmax, 64 * 16) * sizeof(double);
 }
 
 template <int NT, int MODE, int NW>
