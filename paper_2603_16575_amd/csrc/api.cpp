@@ -76,6 +76,7 @@ struct GemmList {
   GemmTask *d = nullptr;
   int64_t tiles = 0;
   GemmShape shape = GEMM_64x64;
+  int form = -1;  // gemm_list_form of the tasks
   int rows_table = 0;
 };
 
@@ -375,6 +376,7 @@ int add_list(mbe3_handle *h, const std::string &name, std::vector<GemmTask> &ts,
   L.shape = shape;
   L.rows_table = rows_table;
   L.tiles = finish_tasks(ts, shape);
+  L.form = gemm_list_form(ts.data(), (int64_t)ts.size());
   L.host = ts;
   const int rc = upload(h, &L.d, ts);
   if (rc) return rc;
@@ -398,7 +400,7 @@ int add_split_lists(mbe3_handle *h, const std::string &name, const std::vector<G
 hipError_t launch_list(mbe3_handle *h, int idx, const GemmBases &b, hipStream_t s) {
   if (idx < 0) return hipSuccess;
   const GemmList &L = h->glists[idx];
-  return launch_gemm_tasks(L.d, (int)L.host.size(), L.tiles, b, L.shape, s);
+  return launch_gemm_tasks(L.d, (int)L.host.size(), L.tiles, b, L.shape, L.form, s);
 }
 
 GemmTask gemm(int a_buf, int64_t a_off, int lda, int transA, int b_buf,
@@ -1896,7 +1898,8 @@ static int run_call_list(mbe3_handle *h, CallTemp &tmp, const char *name,
   if (rc) return rc;
   GemmTask *d = nullptr;
   if ((rc = tmp.upload(&d, ts))) return rc;
-  HIP_TRY(h, launch_gemm_tasks(d, (int)ts.size(), tiles, b, shape, h->stream));
+  HIP_TRY(h, launch_gemm_tasks(d, (int)ts.size(), tiles, b, shape,
+                               gemm_list_form(ts.data(), (int64_t)ts.size()), h->stream));
   return MBE3_OK;
 }
 
@@ -1990,7 +1993,8 @@ static int screen_noalloc_body(mbe3_handle *h, const int32_t *pairs, int64_t n,
                             hipMemcpyHostToDevice, st));
   GemmBases b = bases(h);
   b.p[B_PS2] = S;
-  HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, GEMM_32x32, st));
+  HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, GEMM_32x32,
+                               gemm_list_form(ts.data(), (int64_t)ts.size()), st));
   HIP_TRY(h, launch_s2b(d_wp, (int)n, S, s2b, st));
   // the host tables stay alive until the copies have run
   HIP_TRY(h, hipStreamSynchronize(st));
@@ -2891,7 +2895,8 @@ static int project_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, d
     b.p[B_SLAB] = cs;
     b.p[B_GAMMA] = gc;
     b.rows = d_rows;
-    HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, GEMM_128x128, s));
+    HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, GEMM_128x128,
+                               gemm_list_form(ts.data(), (int64_t)ts.size()), s));
   }
   HIP_TRY(h, launch_fit_scatter(gamma, gc, h->gamma_rows, na, max_nc, h->d_row_lmo, d_goff,
                                 d_gcoff, d_cols, d_col_off, s));
@@ -2980,7 +2985,8 @@ static int pair_k_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, do
     b.p[B_SLAB] = cs;
     b.p[B_GAMMA] = gt;
     b.rows = d_rows;
-    HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, GEMM_64x64, s));
+    HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, GEMM_64x64,
+                               gemm_list_form(ts.data(), (int64_t)ts.size()), s));
   }
   // K blocks (x, y) of every slot over the union of the two domains
   std::vector<GemmTask> kt;
@@ -3052,7 +3058,8 @@ static int pair_k_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, do
     b.p[B_GAMMA] = gt;
     b.p[B_K] = K;
     b.rows = d_krows;
-    HIP_TRY(h, launch_gemm_tasks(d_kt, (int)kt.size(), tiles, b, GEMM_32x32, s));
+    HIP_TRY(h, launch_gemm_tasks(d_kt, (int)kt.size(), tiles, b, GEMM_32x32,
+                               gemm_list_form(kt.data(), (int64_t)kt.size()), s));
   }
   return MBE3_OK;
 }

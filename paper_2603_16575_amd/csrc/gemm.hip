@@ -1,4 +1,6 @@
-// Grouped FP64 GEMM engine on the CDNA matrix cores (v_mfma_f64_16x16x4).
+// Grouped FP64 GEMM engine on the CDNA matrix cores (v_mfma_f64_16x16x4): a
+// general kernel, and gemm_tiles_kernel for the lists that gemm_list_form names
+// (all but those with a single row, column or step along a contiguous dimension).
 //
 // One workgroup (4 wave64) computes one BM x BN tile of one task.  Operand
 // tiles of depth 16 are staged through two LDS buffers with coalesced global
@@ -186,6 +188,266 @@ __global__ __launch_bounds__(256, 2) void gemm_tasks_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same products for lists whose tasks agree on their transpose flags and
+// have at least two elements along the contiguous dimension of either operand
+// (gemm_list_form): 16-byte loads and 16-byte LDS stores.
+//
+// An operand tile (BD x 16) reaches the thread block in 16-byte chunks, in one
+// of two forms fixed at compile time.
+//   rows (K contiguous): 8 chunks per row, kept row by row in LDS, chunk c of
+//     row r at place c ^ (r & 7), so that the 16 rows x 4 k's of an MFMA operand
+//     read fall on all banks evenly;
+//   k-major (M / N contiguous): BD / 2 chunks per k, chunk c of row k at place
+//     c ^ (8 (k & 1)): the two k's of a half-wave's read then lie on different
+//     halves of the banks, without a padded pitch.
+// Every chunk is loaded from an address inside its operand, at 8-byte alignment:
+// one that would reach past the end of its row starts one element earlier and is
+// shifted, one past K is zeroed (the last step only).  Rows past M or N repeat
+// the tile's first one and are not stored.  Each output sums over k in the order
+// of the general kernel, so the results are the same bit for bit.
+// Bound: matrix cores at the projection's 128 x 128 tiles (what is left is the
+// load and store part of a step, which the second workgroup of the CU covers);
+// the general kernel spent 16 loads, 16 stores and their guards on what takes 8
+// and 8 here.  Measured against it: projection of 48 orbitals, 2432 x 7040 slabs,
+// 41.6 ms for 45.9 ms (60.9 TF/s; a 8192^3 library product reaches 72), their pair
+// K 3.59 ms for 4.94 ms, a 160-orbital step's trimer blocks 16.5 ms for 20.5 ms,
+// its pair K 2.75 ms for 3.55 ms, the gradient's products 35.0 ms for 38.4 ms.
+// ---------------------------------------------------------------------------
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <int BD, bool KMAJOR>
+struct TileLoader {
+  static constexpr int NCH = BD / 32;  // chunks per thread
+  const double *base;
+  const int32_t *gather;  // k-major, gathered: row index of k; else null
+  const double *ptr[NCH];  // rows: the chunk's row; k-major: its column
+  int ld, K, c2;           // c2: rows: first k of the thread's chunks
+  int32_t krow[NCH];       // k-major, gathered: rows of the next step's k's
+  bool shift[NCH];         // k-major: the row's odd last element
+  d2 v[NCH];
+
+  // dim: rows of the operand along M / N; x0: first of the tile
+  __device__ __forceinline__ void init(const double *b, const int32_t *rows, int rows_off,
+                                       int ld_, int K_, int dim, int x0, int tid) {
+    base = b;
+    ld = ld_;
+    K = K_;
+    gather = KMAJOR && rows_off >= 0 ? rows + rows_off : nullptr;
+    c2 = 2 * (tid & 7);
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) {
+      if (KMAJOR) {
+        const int c = x0 + 2 * ((tid + 256 * u) % (BD / 2));
+        ptr[u] = base + (c + 1 < dim ? c : c < dim ? c - 1 : x0 + 1 < dim ? x0 : dim - 2);
+        shift[u] = c + 1 == dim;
+      } else {
+        int r = x0 + (tid >> 3) + 32 * u;
+        r = r < dim ? r : x0;
+        ptr[u] = base + (int64_t)(rows_off >= 0 ? rows[rows_off + r] : r) * ld;
+        shift[u] = false;
+      }
+      krow[u] = 0;
+    }
+    if (gather) fetch_rows(0, tid);
+  }
+  __device__ __forceinline__ int k_of(int u, int tid) const { return (tid + 256 * u) / (BD / 2); }
+  __device__ __forceinline__ void fetch_rows(int k0, int tid) {
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) {
+      const int k = k0 + k_of(u, tid);
+      krow[u] = gather[k < K ? k : K - 1];
+    }
+  }
+  __device__ __forceinline__ void load(int k0, int tid) {
+    if (KMAJOR) {
+#pragma unroll
+      for (int u = 0; u < NCH; ++u) {
+        const int k = k0 + k_of(u, tid);
+        const int64_t row = gather ? krow[u] : (k < K ? k : K - 1);
+        v[u] = *(const d2u *)(ptr[u] + row * ld);
+      }
+      if (gather && k0 + 16 < K) fetch_rows(k0 + 16, tid);
+    } else {
+      const int k = k0 + c2;
+      const int64_t o = k + 1 < K ? k : K - 2;
+#pragma unroll
+      for (int u = 0; u < NCH; ++u) v[u] = *(const d2u *)(ptr[u] + o);
+    }
+  }
+  __device__ __forceinline__ void store(double *l, int k0, int tid) {
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) {
+      d2 x = v[u];
+      if (KMAJOR) {
+        const int e = tid + 256 * u, k = e / (BD / 2), c = e % (BD / 2);
+        if (shift[u]) x = d2{x.y, 0.0};
+        if (k0 + k >= K) x = d2{0.0, 0.0};
+        *(d2 *)(l + k * BD + 2 * (c ^ ((k & 1) << 3))) = x;
+      } else {
+        if (k0 + c2 + 1 >= K) x = k0 + c2 < K ? d2{x.y, 0.0} : d2{0.0, 0.0};
+        const int r = (tid >> 3) + 32 * u;
+        *(d2 *)(l + r * 16 + 2 * ((tid & 7) ^ (r & 7))) = x;
+      }
+    }
+  }
+};
+
+// Operand reads: element (x, k) of the tile, x = 16 b + l16, k = kk + lq (b, kk
+// compile-time apart from the wave's first block).
+template <int BD, bool KMAJOR, int NB>
+struct TileReader {
+  int o0, o1;  // k-major: even / odd blocks; rows: the place at kk = 0
+  __device__ __forceinline__ void init(int b0, int l16, int lq) {
+    if (KMAJOR) {
+      const int s = (lq & 1) << 4;
+      const int o = lq * BD + b0 * 16 + l16;
+      o0 = o + (b0 & 1 ? -s : s);
+      o1 = o + (b0 & 1 ? s : -s);
+    } else {
+      o0 = (b0 * 16 + l16) * 16 + 2 * ((lq >> 1) ^ (l16 & 7)) + (lq & 1);
+      o1 = 0;
+    }
+  }
+  __device__ __forceinline__ void read(const double *l, int kk, double *x) const {
+    if (KMAJOR) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) x[b] = l[(b & 1 ? o1 : o0) + kk * BD + b * 16];
+    } else {
+      const int o = o0 ^ kk;  // places kk / 2 on: bits 1.. of the element offset
+#pragma unroll
+      for (int b = 0; b < NB; ++b) x[b] = l[o + b * 256];
+    }
+  }
+};
+
+template <int BM, int BN, bool TA, bool TB>
+__global__ __launch_bounds__(256, 2) void gemm_tiles_kernel(
+    const GemmTask *__restrict__ tasks, int n_tasks, GemmBases bases) {
+  __shared__ __align__(16) double As[2][BM * 16];
+  __shared__ __align__(16) double Bs[2][BN * 16];
+  const int64_t tile = blockIdx.x;
+  int lo = 0, hi = n_tasks - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (tasks[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
+  }
+  const GemmTask t = tasks[lo];
+  const int local = (int)(tile - t.tile_begin);
+  const int m0 = (local / t.tiles_n) * BM;
+  const int n0 = (local % t.tiles_n) * BN;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, lq = lane >> 4;
+  constexpr int TM = BM / 32, TN = BN / 32;  // 16-blocks per wave (2 x 2 waves)
+  const int bm = (wave >> 1) * TM, bn = (wave & 1) * TN;
+
+  TileLoader<BM, TA> la;
+  TileLoader<BN, !TB> lb;
+  la.init(bases.p[t.a_buf] + t.a_off, bases.rows, t.a_rows, t.lda, t.K, t.M, m0, tid);
+  lb.init(bases.p[t.b_buf] + t.b_off, bases.rows, t.b_rows, t.ldb, t.K, t.N, n0, tid);
+  TileReader<BM, TA, TM> ra;
+  TileReader<BN, !TB, TN> rb;
+  ra.init(bm, l16, lq);
+  rb.init(bn, l16, lq);
+
+  d4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+
+  la.load(0, tid);
+  lb.load(0, tid);
+  la.store(As[0], 0, tid);
+  lb.store(Bs[0], 0, tid);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < t.K; k0 += 16) {
+    const bool more = k0 + 16 < t.K;
+    if (more) {
+      la.load(k0 + 16, tid);
+      lb.load(k0 + 16, tid);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 16; kk += 4) {
+      double a[TM], b[TN];
+      ra.read(As[buf], kk, a);
+      rb.read(Bs[buf], kk, b);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    // the other buffer was last read before the previous barrier
+    if (more) {
+      la.store(As[buf ^ 1], k0 + 16, tid);
+      lb.store(Bs[buf ^ 1], k0 + 16, tid);
+    }
+    __syncthreads();
+    buf ^= 1;
+  }
+
+  double *__restrict__ C = bases.p[t.c_buf] + t.c_off;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + (bn + j) * 16 + l16;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int m = m0 + (bm + i) * 16 + lq + 4 * v;
+        double r = t.alpha * acc[i][j][v];
+        if (m < t.M && n < t.N) {
+          double *c = C + (int64_t)m * t.ldc + n;
+          if (t.beta != 0.0) r += t.beta * *c;
+          *c = r;
+        }
+        acc[i][j][v] = r;
+      }
+    }
+  if (t.ct_off < 0) return;
+  // C^T through LDS, one 16 x 16 block of a wave at a time, so that its rows
+  // leave as 128-byte runs too (every wave is past its last operand read)
+  double *__restrict__ CT = bases.p[t.c_buf] + t.ct_off;
+  double *x = &As[0][0] + wave * (16 * 17 > BM * 8 ? BM * 8 : 16 * 17);
+  constexpr bool FITS = BM * 8 >= 16 * 17;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if (FITS) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[(lq + 4 * v) * 17 + l16] = acc[i][j][v];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int m = m0 + (bm + i) * 16 + (FITS ? l16 : lq + 4 * v);
+        const int n = n0 + (bn + j) * 16 + (FITS ? lq + 4 * v : l16);
+        const double r = FITS ? x[l16 * 17 + lq + 4 * v] : acc[i][j][v];
+        if (m < t.M && n < t.N) CT[(int64_t)n * t.ldct + m] = r;
+      }
+      if (FITS) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+}
+
+// Form of a task list: -1 general (also A^T B^T, which no list has); else 2
+// transA + transB of all its tasks.
+int gemm_list_form(const GemmTask *ts, int64_t n) {
+  for (int64_t k = 0; k < n; ++k) {
+    const GemmTask &t = ts[k];
+    if (t.transA != ts[0].transA || t.transB != ts[0].transB) return -1;
+    if ((t.transA ? t.M : t.K) < 2 || (t.transB ? t.K : t.N) < 2) return -1;
+    if (t.transA && t.transB) return -1;
+  }
+  return n > 0 ? 2 * (ts[0].transA != 0) + (ts[0].transB != 0) : -1;
+}
+
 int gemm_tile_m(GemmShape shape) {
   switch (shape) {
     case GEMM_128x128: return 128;
@@ -222,40 +484,40 @@ int64_t gemm_tile_count(const GemmTask &t, GemmShape shape) {
   return (int64_t)((t.M + bm - 1) / bm) * ((t.N + bn - 1) / bn);
 }
 
-hipError_t launch_gemm_tasks(const GemmTask *d_tasks, int n_tasks,
-                             int64_t n_tiles, const GemmBases &bases,
-                             GemmShape shape, hipStream_t s) {
-  if (n_tasks <= 0 || n_tiles <= 0) return hipSuccess;
-  if (n_tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  dim3 grid((unsigned)n_tiles), block(256);
-  switch (shape) {
-    case GEMM_64x64:
-      hipLaunchKernelGGL((gemm_tasks_kernel<64, 64>), grid, block, 0, s, d_tasks,
-                         n_tasks, bases);
+template <int BM, int BN>
+static hipError_t launch_shape(const GemmTask *ts, int n, dim3 grid, const GemmBases &b, int form,
+                               hipStream_t s) {
+  switch (form) {
+    case 0:
+      hipLaunchKernelGGL((gemm_tiles_kernel<BM, BN, false, false>), grid, dim3(256), 0, s, ts, n, b);
       break;
-    case GEMM_128x128:
-      hipLaunchKernelGGL((gemm_tasks_kernel<128, 128>), grid, block, 0, s, d_tasks,
-                         n_tasks, bases);
+    case 1:
+      hipLaunchKernelGGL((gemm_tiles_kernel<BM, BN, false, true>), grid, dim3(256), 0, s, ts, n, b);
       break;
-    case GEMM_32x32:
-      hipLaunchKernelGGL((gemm_tasks_kernel<32, 32>), grid, block, 0, s, d_tasks,
-                         n_tasks, bases);
+    case 2:
+      hipLaunchKernelGGL((gemm_tiles_kernel<BM, BN, true, false>), grid, dim3(256), 0, s, ts, n, b);
       break;
-    case GEMM_32x128:
-      hipLaunchKernelGGL((gemm_tasks_kernel<32, 128>), grid, block, 0, s, d_tasks,
-                         n_tasks, bases);
-      break;
-    case GEMM_64x128:
-      hipLaunchKernelGGL((gemm_tasks_kernel<64, 128>), grid, block, 0, s, d_tasks,
-                         n_tasks, bases);
-      break;
-    case GEMM_96x96:
-      hipLaunchKernelGGL((gemm_tasks_kernel<96, 96>), grid, block, 0, s, d_tasks,
-                         n_tasks, bases);
-      break;
-    default: return hipErrorInvalidValue;
+    default:
+      hipLaunchKernelGGL((gemm_tasks_kernel<BM, BN>), grid, dim3(256), 0, s, ts, n, b);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_gemm_tasks(const GemmTask *d_tasks, int n_tasks,
+                             int64_t n_tiles, const GemmBases &bases,
+                             GemmShape shape, int form, hipStream_t s) {
+  if (n_tasks <= 0 || n_tiles <= 0) return hipSuccess;
+  if (n_tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)n_tiles);
+  switch (shape) {
+    case GEMM_64x64: return launch_shape<64, 64>(d_tasks, n_tasks, grid, bases, form, s);
+    case GEMM_128x128: return launch_shape<128, 128>(d_tasks, n_tasks, grid, bases, form, s);
+    case GEMM_32x32: return launch_shape<32, 32>(d_tasks, n_tasks, grid, bases, form, s);
+    case GEMM_32x128: return launch_shape<32, 128>(d_tasks, n_tasks, grid, bases, form, s);
+    case GEMM_64x128: return launch_shape<64, 128>(d_tasks, n_tasks, grid, bases, form, s);
+    case GEMM_96x96: return launch_shape<96, 96>(d_tasks, n_tasks, grid, bases, form, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace mbe3

@@ -53,7 +53,10 @@ const char *gemm_shape_name(GemmShape shape);
 int64_t gemm_tile_count(const GemmTask &t, GemmShape shape);
 hipError_t launch_gemm_tasks(const GemmTask *d_tasks, int n_tasks,
                              int64_t n_tiles, const GemmBases &bases,
-                             GemmShape shape, hipStream_t s);
+                             GemmShape shape, int form, hipStream_t s);
+// Which kernel a task list can take (host tasks): -1 the general one, else the
+// form of gemm_tiles_kernel its transpose flags name.
+int gemm_list_form(const GemmTask *ts, int64_t n);
 
 // ---------------------------------------------------------------------------
 // Slab regeneration (regen.hip)
