@@ -6,27 +6,56 @@
 // 64x64->128-bit products with the Philox multipliers, high halves xored into
 // the other words with the round key, key bumped by the Weyl constants
 // between rounds.  Box-Muller (1958) on the top 53 bits of words 0 and 1.
-// One thread per element; consecutive threads take consecutive P so the
-// slab is written as coalesced rows of the [n_vir][n_aux] tile.
+// Consecutive threads take consecutive P (rows of the [n_vir][n_aux] slab leave
+// coalesced) and each walks over a, so that the products of the first rounds
+// that do not depend on both (PhiloxColumn) are formed once per column, or on
+// the scalar unit, and no thread divides its element number into indices.
 #include "internal.hpp"
 
 namespace mbe3 {
 
-__device__ __forceinline__ void philox4x64_10(uint64_t &c0, uint64_t &c1,
-                                              uint64_t &c2, uint64_t &c3,
-                                              uint64_t k0, uint64_t k1) {
-  const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
-  const uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r) { k0 += W0; k1 += W1; }
-    const uint64_t hi0 = __umul64hi(M0, c0), lo0 = M0 * c0;
-    const uint64_t hi1 = __umul64hi(M1, c2), lo1 = M1 * c2;
-    const uint64_t n0 = hi1 ^ c1 ^ k0;
-    const uint64_t n2 = hi0 ^ c3 ^ k1;
-    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
+constexpr uint64_t PHILOX_M0 = 0xD2E7470EE14C6C93ull, PHILOX_M1 = 0xCA5A826395121157ull;
+constexpr uint64_t PHILOX_W0 = 0x9E3779B97F4A7C15ull, PHILOX_W1 = 0xBB67AE8584CAA73Bull;
+
+// The blocks at counters (P, a, i, 0) of one column P under key (k0, k1).  Word 0
+// meets only P until the third round and word 2 only i and a, so of the 20
+// products of a block 4 depend on P and i alone (kept here) and 1 on a and i (one
+// for a whole wave where a is uniform).  Measured with the index arithmetic gone:
+// slabs at 101 G elements/s for 74 (48 orbitals, 2432 x 7040: 8.1 ms for 11.1 ms).
+struct PhiloxColumn {
+  uint64_t k0, k1, n0, m1, m2, hi3, lo3;
+  __device__ __forceinline__ PhiloxColumn(uint64_t P, uint64_t i, uint64_t key0, uint64_t key1)
+      : k0(key0), k1(key1) {
+    n0 = __umul64hi(PHILOX_M1, i) ^ k0;                                // round 1: word 0 ^ a
+    const uint64_t n2 = __umul64hi(PHILOX_M0, P) ^ k1;                 //          word 2
+    m1 = PHILOX_M1 * n2;                                               // round 2: word 1
+    m2 = PHILOX_M0 * P ^ (k1 + PHILOX_W1);                             //   word 2 ^ hi(M0 n0)
+    const uint64_t m0 =                                                //   word 0
+        __umul64hi(PHILOX_M1, n2) ^ (PHILOX_M1 * i) ^ (k0 + PHILOX_W0);
+    hi3 = __umul64hi(PHILOX_M0, m0);                                   // round 3
+    lo3 = PHILOX_M0 * m0;
   }
-}
+  // words 0 and 1 of the block at row a
+  __device__ __forceinline__ void draw(uint64_t a, uint64_t &w0, uint64_t &w1) const {
+    const uint64_t x = n0 ^ a, y = m2 ^ __umul64hi(PHILOX_M0, x);
+    uint64_t q0 = k0 + 2 * PHILOX_W0, q1 = k1 + 2 * PHILOX_W1;
+    uint64_t c0 = __umul64hi(PHILOX_M1, y) ^ m1 ^ q0, c1 = PHILOX_M1 * y;
+    uint64_t c2 = hi3 ^ (PHILOX_M0 * x) ^ q1, c3 = lo3;
+#pragma unroll
+    for (int r = 3; r < 10; ++r) {
+      q0 += PHILOX_W0;
+      q1 += PHILOX_W1;
+      const uint64_t hi0 = __umul64hi(PHILOX_M0, c0), lo0 = PHILOX_M0 * c0;
+      const uint64_t hi1 = __umul64hi(PHILOX_M1, c2), lo1 = PHILOX_M1 * c2;
+      c0 = hi1 ^ c1 ^ q0;
+      c2 = hi0 ^ c3 ^ q1;
+      c1 = lo1;
+      c3 = lo0;
+    }
+    w0 = c0;
+    w1 = c1;
+  }
+};
 
 __device__ __forceinline__ double box_muller(uint64_t w0, uint64_t w1) {
   const double u1 = ((double)(w0 >> 11) + 0.5) * 0x1p-53;
@@ -40,32 +69,33 @@ __device__ __forceinline__ double box_muller(uint64_t w0, uint64_t w1) {
 // the gradient probe direction Delta (stream 10); cb = 1, cd = t the shifted
 // slab B + t Delta of a finite-difference check.  cb and cd are uniform over
 // the launch, so the skipped draw is a uniform branch.
+// Workgroup (x, y, z): columns 256 x .., rows REGEN_ROWS y .., batch member z.
+constexpr int REGEN_ROWS = 16;
 __global__ __launch_bounds__(256) void regen_slab_kernel(
-    double *__restrict__ out, int i0, int nb, int n_vir, int n_aux,
+    double *__restrict__ out, int i0, int n_vir, int n_aux,
     uint64_t seed, const double *__restrict__ w_ia,
     const double *__restrict__ w_iP, double cb, double cd) {
-  const int64_t per = (int64_t)n_vir * n_aux;
-  const int64_t total = per * nb;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int b = (int)(e / per);
-    const int64_t r = e - (int64_t)b * per;
-    const int a = (int)(r / n_aux);
-    const int P = (int)(r - (int64_t)a * n_aux);
-    const int i = i0 + b;
+  const int P = blockIdx.x * 256 + threadIdx.x;
+  if (P >= n_aux) return;
+  const int i = i0 + (int)blockIdx.z;
+  const int a0 = blockIdx.y * REGEN_ROWS, a1 = min(n_vir, a0 + REGEN_ROWS);
+  const double wp = w_iP[(int64_t)i * n_aux + P];
+  const double *wa = w_ia + (int64_t)i * n_vir;
+  double *o = out + (int64_t)blockIdx.z * n_vir * n_aux + P;
+  const PhiloxColumn cs(P, i, seed, 0ull), cp(P, i, seed, (uint64_t)PROBE_STREAM);
+  for (int a = a0; a < a1; ++a) {
     double z = 0.0;
+    uint64_t w0, w1;
     if (cb != 0.0) {
-      uint64_t c0 = (uint64_t)P, c1 = (uint64_t)a, c2 = (uint64_t)i, c3 = 0;
-      philox4x64_10(c0, c1, c2, c3, seed, 0ull);
-      z = box_muller(c0, c1);
+      cs.draw(a, w0, w1);
+      z = box_muller(w0, w1);
       if (cb != 1.0) z *= cb;
     }
     if (cd != 0.0) {
-      uint64_t c0 = (uint64_t)P, c1 = (uint64_t)a, c2 = (uint64_t)i, c3 = 0;
-      philox4x64_10(c0, c1, c2, c3, seed, (uint64_t)PROBE_STREAM);
-      z += cd * box_muller(c0, c1);
+      cp.draw(a, w0, w1);
+      z += cd * box_muller(w0, w1);
     }
-    out[e] = (z * w_ia[(int64_t)i * n_vir + a]) * w_iP[(int64_t)i * n_aux + P];
+    o[(int64_t)a * n_aux] = (z * wa[a]) * wp;
   }
 }
 
@@ -99,31 +129,29 @@ __device__ __forceinline__ void split3(double x, uint16_t *dst, int64_t ps) {
 // the transposed layout [b][P][a] (a fastest, row pitch ldk >= n_vir, zero
 // padded), the K-contiguous operand of the projection.  With an explicit
 // slab (device [n_occ][n_vir][n_aux]) its values are split instead.
+// Workgroup (x, y, z): rows a = 256 x .., columns REGEN_ROWS y .., member z; the
+// column is uniform here, so its share of the generator is scalar work.
 __global__ __launch_bounds__(256) void regen_split_kernel(
-    uint16_t *__restrict__ planes, int64_t ps, int i0, int nb, int n_vir,
+    uint16_t *__restrict__ planes, int64_t ps, int i0, int n_vir,
     int n_aux, int ldk, uint64_t seed, const double *__restrict__ w_ia,
     const double *__restrict__ w_iP, const double *__restrict__ slab) {
-  const int64_t per = (int64_t)n_aux * ldk;
-  const int64_t total = per * nb;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int b = (int)(e / per);
-    const int64_t r = e - (int64_t)b * per;
-    const int P = (int)(r / ldk);
-    const int a = (int)(r - (int64_t)P * ldk);
-    const int i = i0 + b;
+  const int a = blockIdx.x * 256 + threadIdx.x;
+  if (a >= ldk) return;
+  const int i = i0 + (int)blockIdx.z;
+  const int P0 = blockIdx.y * REGEN_ROWS, P1 = min(n_aux, P0 + REGEN_ROWS);
+  const double wa = !slab && a < n_vir ? w_ia[(int64_t)i * n_vir + a] : 0.0;
+  for (int P = P0; P < P1; ++P) {
     double x = 0.0;
     if (a < n_vir) {
       if (slab) {
         x = slab[((int64_t)i * n_vir + a) * n_aux + P];
       } else {
-        uint64_t c0 = (uint64_t)P, c1 = (uint64_t)a, c2 = (uint64_t)i, c3 = 0;
-        philox4x64_10(c0, c1, c2, c3, seed, 0ull);
-        const double z = box_muller(c0, c1);
-        x = (z * w_ia[(int64_t)i * n_vir + a]) * w_iP[(int64_t)i * n_aux + P];
+        uint64_t w0, w1;
+        PhiloxColumn(P, i, seed, 0ull).draw(a, w0, w1);
+        x = (box_muller(w0, w1) * wa) * w_iP[(int64_t)i * n_aux + P];
       }
     }
-    split3(x, planes + e, ps);
+    split3(x, planes + ((int64_t)blockIdx.z * n_aux + P) * ldk + a, ps);
   }
 }
 
@@ -184,11 +212,16 @@ hipError_t launch_regen_split(uint16_t *planes, int64_t ps, int i0, int nb,
                               int n_vir, int n_aux, int ldk, uint64_t seed,
                               const double *w_ia, const double *w_iP,
                               const double *slab, hipStream_t s) {
-  const int64_t total = (int64_t)n_aux * ldk * nb;
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(regen_split_kernel, dim3((unsigned)grid_for(total)), dim3(256),
-                     0, s, planes, ps, i0, nb, n_vir, n_aux, ldk, seed, w_ia,
-                     w_iP, slab);
+  // batch members and column groups in launches of at most 65535
+  const int gy = (n_aux + REGEN_ROWS - 1) / REGEN_ROWS;
+  if (nb <= 0 || gy <= 0) return hipSuccess;
+  if (gy > 65535) return hipErrorInvalidValue;
+  for (int b = 0; b < nb; b += 65535)
+    hipLaunchKernelGGL(regen_split_kernel,
+                       dim3((unsigned)((ldk + 255) / 256), (unsigned)gy,
+                            (unsigned)(nb - b < 65535 ? nb - b : 65535)),
+                       dim3(256), 0, s, planes + (int64_t)b * n_aux * ldk, ps, i0 + b, n_vir,
+                       n_aux, ldk, seed, w_ia, w_iP, slab);
   return hipGetLastError();
 }
 
@@ -215,15 +248,17 @@ hipError_t launch_split_rows_fixed(const double *x, int64_t rows, int cols, int6
 hipError_t launch_regen_slab(double *out, int i0, int nb, int n_vir, int n_aux,
                              uint64_t seed, const double *w_ia,
                              const double *w_iP, double cb, double cd, hipStream_t s) {
-  const int64_t total = (int64_t)n_vir * n_aux * nb;
-  if (total <= 0) return hipSuccess;
-  int64_t blocks = (total + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(regen_slab_kernel, dim3((unsigned)blocks), dim3(256), 0, s,
-                     out, i0, nb, n_vir, n_aux, seed, w_ia, w_iP, cb, cd);
+  const int gy = (n_vir + REGEN_ROWS - 1) / REGEN_ROWS;
+  if (nb <= 0 || gy <= 0 || n_aux <= 0) return hipSuccess;
+  if (gy > 65535) return hipErrorInvalidValue;
+  for (int b = 0; b < nb; b += 65535)
+    hipLaunchKernelGGL(regen_slab_kernel,
+                       dim3((unsigned)((n_aux + 255) / 256), (unsigned)gy,
+                            (unsigned)(nb - b < 65535 ? nb - b : 65535)),
+                       dim3(256), 0, s, out + (int64_t)b * n_vir * n_aux, i0 + b, n_vir, n_aux,
+                       seed, w_ia, w_iP, cb, cd);
   return hipGetLastError();
 }
-
 
 // ---------------------------------------------------------------------------
 // Sparse fitting domains (eq. sparse_fit_metric).  s_fit[i][P] is the sum
@@ -250,10 +285,11 @@ __global__ __launch_bounds__(256) void fit_metric_kernel(
   } else {
     const double wp = w_iP[e];
     const double *wa = w_ia + (int64_t)i * n_vir;
+    const PhiloxColumn cs(P, i, seed, 0ull);
     for (int a = 0; a < n_vir; ++a) {
-      uint64_t c0 = (uint64_t)P, c1 = (uint64_t)a, c2 = (uint64_t)i, c3 = 0;
-      philox4x64_10(c0, c1, c2, c3, seed, 0ull);
-      const double v = (box_muller(c0, c1) * wa[a]) * wp;
+      uint64_t w0, w1;
+      cs.draw(a, w0, w1);
+      const double v = (box_muller(w0, w1) * wa[a]) * wp;
       s += v * v;
     }
   }
@@ -293,29 +329,33 @@ __global__ __launch_bounds__(256) void fit_mask_kernel(
 // domain columns cols[col_off[i] .. col_off[i + 1]) (nc of them),
 //   out[out_off[b] + a * nc + c] = B_i[a][cols[col_off[i] + c]],
 // each element regenerated exactly as regen_slab_kernel writes it (or read
-// from a given slab).  One workgroup row (blockIdx.y) per LMO of the batch.
+// from a given slab).  Workgroup (x, y, z): 64 kept columns, REGEN_ROWS rows for
+// each of its four waves, LMO z of the batch.
 __global__ __launch_bounds__(256) void regen_cols_kernel(
     double *__restrict__ out, const int64_t *__restrict__ out_off,
     const int32_t *__restrict__ cols, const int32_t *__restrict__ col_off, int i0,
     int n_vir, int n_aux, uint64_t seed, const double *__restrict__ w_ia,
     const double *__restrict__ w_iP, const double *__restrict__ slab) {
-  const int i = i0 + (int)blockIdx.y;
+  const int i = i0 + (int)blockIdx.z;
   const int c0 = col_off[i], nc = col_off[i + 1] - c0;
-  const int64_t total = (int64_t)n_vir * nc;
-  double *o = out + out_off[blockIdx.y];
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int a = (int)(e / nc);
-    const int P = cols[c0 + (int)(e - (int64_t)a * nc)];
-    double v;
-    if (slab) {
-      v = slab[((int64_t)i * n_vir + a) * n_aux + P];
-    } else {
-      uint64_t k0 = (uint64_t)P, k1 = (uint64_t)a, k2 = (uint64_t)i, k3 = 0;
-      philox4x64_10(k0, k1, k2, k3, seed, 0ull);
-      v = (box_muller(k0, k1) * w_ia[(int64_t)i * n_vir + a]) * w_iP[(int64_t)i * n_aux + P];
-    }
-    o[e] = v;
+  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
+  if (c >= nc) return;
+  const int P = cols[c0 + c];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int a0 = (blockIdx.y * 4 + wave) * REGEN_ROWS, a1 = min(n_vir, a0 + REGEN_ROWS);
+  double *o = out + out_off[blockIdx.z] + c;
+  if (slab) {
+    const double *b = slab + (int64_t)i * n_vir * n_aux + P;
+    for (int a = a0; a < a1; ++a) o[(int64_t)a * nc] = b[(int64_t)a * n_aux];
+    return;
+  }
+  const double wp = w_iP[(int64_t)i * n_aux + P];
+  const double *wa = w_ia + (int64_t)i * n_vir;
+  const PhiloxColumn cs(P, i, seed, 0ull);
+  for (int a = a0; a < a1; ++a) {
+    uint64_t w0, w1;
+    cs.draw(a, w0, w1);
+    o[(int64_t)a * nc] = (box_muller(w0, w1) * wa[a]) * wp;
   }
 }
 
@@ -343,10 +383,11 @@ hipError_t launch_regen_cols(double *out, const int64_t *out_off, const int32_t 
                              const double *w_iP, const double *slab, hipStream_t s) {
   if (nb <= 0 || max_elems <= 0) return hipSuccess;
   if (nb > 65535) return hipErrorInvalidValue;
-  int64_t gx = (max_elems + 255) / 256;
-  if (gx > 1024) gx = 1024;
-  hipLaunchKernelGGL(regen_cols_kernel, dim3((unsigned)gx, (unsigned)nb), dim3(256), 0, s,
-                     out, out_off, cols, col_off, i0, n_vir, n_aux, seed, w_ia, w_iP, slab);
+  const int64_t gx = (max_elems / n_vir + 63) / 64;  // max_elems: n_vir times the most columns
+  const int gy = (n_vir + 4 * REGEN_ROWS - 1) / (4 * REGEN_ROWS);
+  if (gy > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(regen_cols_kernel, dim3((unsigned)gx, (unsigned)gy, (unsigned)nb), dim3(256),
+                     0, s, out, out_off, cols, col_off, i0, n_vir, n_aux, seed, w_ia, w_iP, slab);
   return hipGetLastError();
 }
 
@@ -369,28 +410,27 @@ hipError_t launch_fit_scatter(double *g, const double *gc, int64_t rows, int n_a
 __global__ __launch_bounds__(256) void regen_gauss_kernel(double *__restrict__ out, int i0,
                                                           int nb, int n_rows, int n_vir,
                                                           uint64_t seed, uint64_t stream) {
-  const int64_t per = (int64_t)n_rows * n_vir;
-  const int64_t total = per * nb;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int b = (int)(e / per);
-    const int64_t r = e - (int64_t)b * per;
-    const int srow = (int)(r / n_vir);
-    const int a = (int)(r - (int64_t)srow * n_vir);
-    uint64_t c0 = (uint64_t)a, c1 = (uint64_t)srow, c2 = (uint64_t)(i0 + b), c3 = 0;
-    philox4x64_10(c0, c1, c2, c3, seed, stream);
-    out[e] = box_muller(c0, c1);
+  const int a = blockIdx.x * 256 + threadIdx.x;
+  if (a >= n_vir) return;
+  const int s0 = blockIdx.y * REGEN_ROWS, s1 = min(n_rows, s0 + REGEN_ROWS);
+  for (int b = blockIdx.z; b < nb; b += gridDim.z) {
+    const PhiloxColumn cs(a, i0 + b, seed, stream);
+    for (int r = s0; r < s1; ++r) {
+      uint64_t w0, w1;
+      cs.draw(r, w0, w1);
+      out[((int64_t)b * n_rows + r) * n_vir + a] = box_muller(w0, w1);
+    }
   }
 }
 
 hipError_t launch_regen_gauss(double *out, int i0, int nb, int n_rows, int n_vir,
                               uint64_t seed, uint64_t stream, hipStream_t s) {
-  const int64_t total = (int64_t)nb * n_rows * n_vir;
-  if (total <= 0) return hipSuccess;
-  int64_t blocks = (total + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(regen_gauss_kernel, dim3((unsigned)blocks), dim3(256), 0, s, out, i0, nb,
-                     n_rows, n_vir, seed, stream);
+  if (nb <= 0 || n_rows <= 0 || n_vir <= 0) return hipSuccess;
+  const int gy = (n_rows + REGEN_ROWS - 1) / REGEN_ROWS;
+  hipLaunchKernelGGL(regen_gauss_kernel,
+                     dim3((unsigned)((n_vir + 255) / 256), (unsigned)gy,
+                          (unsigned)(nb < 65535 ? nb : 65535)),
+                     dim3(256), 0, s, out, i0, nb, n_rows, n_vir, seed, stream);
   return hipGetLastError();
 }
 
