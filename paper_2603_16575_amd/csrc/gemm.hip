@@ -436,14 +436,12 @@ __global__ __launch_bounds__(256, 2) void gemm_tiles_kernel(
     }
 }
 
-// Form of a task list: -1 general (also A^T B^T, which no list has); else 2
-// transA + transB of all its tasks.
+// Form of a task list: -1 general; else 2 transA + transB of all its tasks.
 int gemm_list_form(const GemmTask *ts, int64_t n) {
   for (int64_t k = 0; k < n; ++k) {
     const GemmTask &t = ts[k];
     if (t.transA != ts[0].transA || t.transB != ts[0].transB) return -1;
     if ((t.transA ? t.M : t.K) < 2 || (t.transB ? t.K : t.N) < 2) return -1;
-    if (t.transA && t.transB) return -1;
   }
   return n > 0 ? 2 * (ts[0].transA != 0) + (ts[0].transB != 0) : -1;
 }
@@ -496,6 +494,9 @@ static hipError_t launch_shape(const GemmTask *ts, int n, dim3 grid, const GemmB
       break;
     case 2:
       hipLaunchKernelGGL((gemm_tiles_kernel<BM, BN, true, false>), grid, dim3(256), 0, s, ts, n, b);
+      break;
+    case 3:
+      hipLaunchKernelGGL((gemm_tiles_kernel<BM, BN, true, true>), grid, dim3(256), 0, s, ts, n, b);
       break;
     default:
       hipLaunchKernelGGL((gemm_tasks_kernel<BM, BN>), grid, dim3(256), 0, s, ts, n, b);
