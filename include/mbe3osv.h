@@ -436,8 +436,7 @@ int mbe3_pm_localize(const double *C, const int32_t *ao_off, int32_t n_ao, int32
  * diagonal slots are T^MBE_ii), or any caller blocks.  e: device [n].
  * Uses the pair bases of the handle's last eager fragment_solve or
  * mbe3_pair_basis call (prepares them when there was none), allocates and
- * frees its blocks (about 3 sum r_i r_j + 2 sum D_i D_j + sum D_i r_j
- * doubles) inside the call, so it cannot be recorded; synchronises the
+ * frees its blocks (about 2 sum r_i r_j + 3 sum r_i D_j doubles) inside the call, so it cannot be recorded; synchronises the
  * stream.
  * MBE3_EINVAL for a bad pair or argument or while recording.
  */

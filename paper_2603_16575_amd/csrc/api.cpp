@@ -1858,46 +1858,95 @@ struct CallTemp {
   }
 };
 
-// Pairs of a screening / weak-pair call, checked and laid out: r_i x r_j
-// blocks, D_i x D_j blocks and the X_i^T (.) temporaries (D_i x r_j).
+// Pairs of one second LMO j in a screening / weak-pair call: their blocks' rows,
+// row after row (a new group where the rows reach WEAK_GROUP_ROWS).
+static const int WEAK_GROUP_ROWS = 1 << 20;
+struct WeakGroup {
+  int j, m;               // m: sum of r_i
+  int64_t k_off, t_off;   // first block of the group in either layout
+  std::vector<int> first; // i of each pair
+};
+
+// Pairs of a screening / weak-pair call, checked and laid out by their second
+// LMO (WeakPair): totals of the r_i x r_j and the r_i x D_j blocks.
 static int weak_layout(mbe3_handle *h, const int32_t *pairs, int64_t n, bool ordered,
-                       std::vector<WeakPair> &wp, int64_t *k_tot, int64_t *t_tot,
-                       int64_t *p_tot, std::vector<int64_t> &p_off) {
+                       std::vector<WeakPair> &wp, std::vector<WeakGroup> &groups,
+                       int64_t *k_tot, int64_t *t_tot) {
   if (n > 0x7fffffffLL / 4) return h->fail(MBE3_EINVAL, "too many pairs (%lld)", (long long)n);
   wp.resize(n);
-  p_off.resize(n);
-  int64_t ko = 0, to = 0, po = 0;
+  std::vector<int> at(h->n_occ, -1), group(n);
   for (int64_t k = 0; k < n; ++k) {
     const int i = pairs[2 * k], j = pairs[2 * k + 1];
     if (i < 0 || j < 0 || i >= h->n_occ || j >= h->n_occ || i == j || (ordered && i > j))
       return h->fail(MBE3_EINVAL, "pair %lld (%d, %d) is not %s", (long long)k, i, j,
                      ordered ? "0 <= i < j < n_occ" : "two distinct LMOs");
+    if (at[j] < 0 || groups[at[j]].m > WEAK_GROUP_ROWS) {
+      at[j] = (int)groups.size();
+      groups.push_back({j, 0, 0, 0, {}});
+    }
+    WeakGroup &g = groups[group[k] = at[j]];
     WeakPair w;
     w.i = i; w.j = j; w.ri = h->r[i]; w.rj = h->r[j];
     w.Di = h->sD[i]; w.Dj = h->sD[j];  // the diagonal slots i and j
-    w.k_off = ko; w.t_off = to;
+    w.k_off = g.m;                     // row in the group, for now
+    w.t_off = 0;
     w.ei = h->et_off[i]; w.ej = h->et_off[j];
+    w.xi = h->x_off[i];
     wp[k] = w;
-    p_off[k] = po;
-    ko += (int64_t)w.ri * w.rj;
-    to += (int64_t)w.Di * w.Dj;
-    po += (int64_t)w.Di * w.rj;
+    g.m += w.ri;
+    g.first.push_back(i);
   }
-  *k_tot = ko; *t_tot = to; *p_tot = po;
+  int64_t ko = 0, to = 0;
+  for (WeakGroup &g : groups) {
+    g.k_off = ko;
+    g.t_off = to;
+    ko += (int64_t)g.m * h->r[g.j];
+    to += (int64_t)g.m * h->sD[g.j];
+  }
+  for (int64_t k = 0; k < n; ++k) {
+    WeakPair &w = wp[k];
+    const WeakGroup &g = groups[group[k]];
+    const int64_t row = w.k_off;
+    w.k_off = g.k_off + row * w.rj;
+    w.t_off = g.t_off + row * w.Dj;
+  }
+  *k_tot = ko; *t_tot = to;
   return MBE3_OK;
+}
+
+// S_(i,j) = Q_i^T Q_j of every listed pair, one product per second LMO over the
+// gathered rows of its partners.
+static void weak_S_tasks(const mbe3_handle *h, const std::vector<WeakGroup> &groups,
+                         std::vector<GemmTask> &ts, std::vector<int32_t> &rows) {
+  const int nv = h->n_vir;
+  for (const WeakGroup &g : groups) {
+    const int rj = h->r[g.j];
+    GemmTask t = gemm(B_Q, 0, nv, 0, B_Q, h->q_off[g.j] * nv, nv, 1, B_PS2, g.k_off, rj, g.m,
+                      rj, nv);
+    t.a_rows = (int32_t)rows.size();
+    for (int i : g.first)
+      for (int mu = 0; mu < h->r[i]; ++mu) rows.push_back((int32_t)(h->q_off[i] + mu));
+    ts.push_back(t);
+  }
 }
 
 // One call-time task list: bounds-checked against sz, tiled, uploaded and
 // launched on the handle's stream.
 static int run_call_list(mbe3_handle *h, CallTemp &tmp, const char *name,
-                         std::vector<GemmTask> &ts, const int64_t *sz, const GemmBases &b,
-                         GemmShape shape) {
+                         std::vector<GemmTask> &ts, const int64_t *sz, GemmBases b,
+                         GemmShape shape,
+                         const std::vector<int32_t> &rows = std::vector<int32_t>()) {
   if (ts.empty()) return MBE3_OK;
   const int64_t tiles = finish_tasks(ts, shape);
-  int rc = check_gemm_list(h, name, ts, sz, std::vector<int32_t>(), shape);
+  int rc = check_gemm_list(h, name, ts, sz, rows, shape);
   if (rc) return rc;
   GemmTask *d = nullptr;
   if ((rc = tmp.upload(&d, ts))) return rc;
+  if (!rows.empty()) {
+    int32_t *d_rows = nullptr;
+    if ((rc = tmp.upload(&d_rows, rows))) return rc;
+    b.rows = d_rows;
+  }
   HIP_TRY(h, launch_gemm_tasks(d, (int)ts.size(), tiles, b, shape,
                                gemm_list_form(ts.data(), (int64_t)ts.size()), h->stream));
   return MBE3_OK;
@@ -1959,12 +2008,13 @@ static int screen_noalloc_body(mbe3_handle *h, const int32_t *pairs, int64_t n,
     return h->fail(MBE3_EINVAL, "pairs and s2b required for n > 0");
   if (n == 0) return MBE3_OK;
   std::vector<WeakPair> wp;
-  std::vector<int64_t> p_off;
-  int64_t ko, to, po;
-  int rc = weak_layout(h, pairs, n, false, wp, &ko, &to, &po, p_off);
+  std::vector<WeakGroup> groups;
+  int64_t ko, to;
+  int rc = weak_layout(h, pairs, n, false, wp, groups, &ko, &to);
   if (rc) return rc;
   const int nv = h->n_vir;
   std::vector<GemmTask> ts;
+  // a task per pair here, not a row table: the scratch takes the pairs it took
   for (const WeakPair &w : wp)  // S_(i,j) = Q_i^T Q_j (rows of the packed Q)
     ts.push_back(gemm(B_Q, h->q_off[w.i] * nv, nv, 0, B_Q, h->q_off[w.j] * nv, nv, 1,
                       B_PS2, w.k_off, w.rj, w.ri, w.rj, nv));
@@ -2631,25 +2681,23 @@ static int screen_body(mbe3_handle *h, const int32_t *pairs, int64_t n, double *
     return h->fail(MBE3_EINVAL, "pairs and s2b required for n > 0");
   if (n == 0) return MBE3_OK;
   std::vector<WeakPair> wp;
-  std::vector<int64_t> p_off;
-  int64_t ko, to, po;
-  int rc = weak_layout(h, pairs, n, false, wp, &ko, &to, &po, p_off);
+  std::vector<WeakGroup> groups;
+  int64_t ko, to;
+  int rc = weak_layout(h, pairs, n, false, wp, groups, &ko, &to);
   if (rc) return rc;
   CallTemp tmp(h);
   double *S = nullptr;
   WeakPair *d_wp = nullptr;
   if ((rc = tmp.alloc(&S, ko)) || (rc = tmp.upload(&d_wp, wp))) return rc;
-  const int nv = h->n_vir;
   std::vector<GemmTask> ts;
-  for (const WeakPair &w : wp)  // S_(i,j) = Q_i^T Q_j (rows of the packed Q)
-    ts.push_back(gemm(B_Q, h->q_off[w.i] * nv, nv, 0, B_Q, h->q_off[w.j] * nv, nv, 1,
-                      B_PS2, w.k_off, w.rj, w.ri, w.rj, nv));
+  std::vector<int32_t> rows;
+  weak_S_tasks(h, groups, ts, rows);
   int64_t sz[B_COUNT];
   base_sizes(h, sz);
   sz[B_PS2] = ko;
   GemmBases b = bases(h);
   b.p[B_PS2] = S;
-  if ((rc = run_call_list(h, tmp, "screen S", ts, sz, b, GEMM_32x32))) return rc;
+  if ((rc = run_call_list(h, tmp, "screen S", ts, sz, b, GEMM_128x32, rows))) return rc;
   HIP_TRY(h, launch_s2b(d_wp, (int)n, S, s2b, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return MBE3_OK;
@@ -2662,74 +2710,82 @@ static int weak_body(mbe3_handle *h, const int32_t *pairs, int64_t n, const doub
     return h->fail(MBE3_EINVAL, "pairs, gamma, W and e required for n > 0");
   if (n == 0) return MBE3_OK;
   std::vector<WeakPair> wp;
-  std::vector<int64_t> p_off;
-  int64_t ko, to, po;
-  int rc = weak_layout(h, pairs, n, true, wp, &ko, &to, &po, p_off);
+  std::vector<WeakGroup> groups;
+  int64_t ko, to;
+  int rc = weak_layout(h, pairs, n, true, wp, groups, &ko, &to);
   if (rc) return rc;
   // X, eps~ and ranks of the diagonal slots: those of the last eager
   // preparation (fragment_solve, mbe3_pair_basis), else prepared here
   if (!h->bases_done && (rc = prepare_bases(h))) return rc;
   CallTemp tmp(h);
-  double *Kb = nullptr, *Sb = nullptr, *Mb = nullptr, *Pb = nullptr, *Kt = nullptr,
-         *Dt = nullptr;
+  const int64_t nx = h->x_off[h->n_occ];  // the diagonal slots' X
+  double *Kb = nullptr, *Sb = nullptr, *TX = nullptr, *BX = nullptr, *KX = nullptr,
+         *SX = nullptr;
   WeakPair *d_wp = nullptr;
-  if ((rc = tmp.alloc(&Kb, ko)) || (rc = tmp.alloc(&Sb, ko)) || (rc = tmp.alloc(&Mb, ko)) ||
-      (rc = tmp.alloc(&Pb, po)) || (rc = tmp.alloc(&Kt, to)) || (rc = tmp.alloc(&Dt, to)) ||
+  if ((rc = tmp.alloc(&Kb, ko)) || (rc = tmp.alloc(&Sb, ko)) || (rc = tmp.alloc(&TX, nx)) ||
+      (rc = tmp.alloc(&BX, nx)) || (rc = tmp.alloc(&KX, to)) || (rc = tmp.alloc(&SX, 2 * to)) ||
       (rc = tmp.upload(&d_wp, wp)))
     return rc;
-  const int nv = h->n_vir, na = h->n_aux;
-  std::vector<GemmTask> lk, ls, lm1, lm2, lxk, lkx, lxm, lmx;
-  for (int64_t k = 0; k < n; ++k) {
-    const WeakPair &w = wp[k];
-    const auto fi = h->grow.find(key2(w.i, w.i)), fj = h->grow.find(key2(w.j, w.j));
-    if (fi == h->grow.end() || fj == h->grow.end())  // every LMO projects onto itself
-      return h->fail(MBE3_EINVAL, "internal: no gamma rows of (%d,%d) or (%d,%d)", w.i, w.i,
-                     w.j, w.j);
-    const int64_t gi = fi->second, gj = fj->second;
-    // K_(i,j) = Gamma~_(i,i) Gamma~_(j,j)^T (eq. osv_weak_k)
-    lk.push_back(gemm(B_GAMMA, gi * na, na, 0, B_GAMMA, gj * na, na, 1, B_PK, w.k_off,
-                      w.rj, w.ri, w.rj, na));
-    // S_(i,j) = Q_i^T Q_j
-    ls.push_back(gemm(B_Q, h->q_off[w.i] * nv, nv, 0, B_Q, h->q_off[w.j] * nv, nv, 1,
-                      B_PS2, w.k_off, w.rj, w.ri, w.rj, nv));
-    // M = T_ii S_(i,j) + S_(i,j) T_jj, T_ii the diagonal slot blocks of W
-    lm1.push_back(gemm(B_W, h->k_off[w.i], w.ri, 0, B_PS2, w.k_off, w.rj, 0, B_PM, w.k_off,
-                       w.rj, w.ri, w.rj, w.ri));
-    lm2.push_back(gemm(B_PS2, w.k_off, w.rj, 0, B_W, h->k_off[w.j], w.rj, 0, B_PM, w.k_off,
-                       w.rj, w.ri, w.rj, w.rj, 1.0, 1.0));
-    // K~ = X_i^T K X_j and D~ = X_i^T M X_j (X: d x D, row-major)
-    lxk.push_back(gemm(B_X, h->x_off[w.i], w.Di, 1, B_PK, w.k_off, w.rj, 0, B_PP, p_off[k],
-                       w.rj, w.Di, w.rj, w.ri));
-    lkx.push_back(gemm(B_PP, p_off[k], w.rj, 0, B_X, h->x_off[w.j], w.Dj, 0, B_PKT, w.t_off,
-                       w.Dj, w.Di, w.Dj, w.rj));
-    lxm.push_back(gemm(B_X, h->x_off[w.i], w.Di, 1, B_PM, w.k_off, w.rj, 0, B_PP, p_off[k],
-                       w.rj, w.Di, w.rj, w.ri));
-    lmx.push_back(gemm(B_PP, p_off[k], w.rj, 0, B_X, h->x_off[w.j], w.Dj, 0, B_PDT, w.t_off,
-                       w.Dj, w.Di, w.Dj, w.rj));
+  const int na = h->n_aux;
+  std::vector<GemmTask> lk, ls, ltx, lbx, lkx, lsx, lsb;
+  std::vector<int32_t> rows_k, rows_s;
+  std::vector<char> left(h->n_occ, 0);
+  for (const WeakGroup &g : groups) {
+    const int j = g.j, rj = h->r[j], Dj = h->sD[j];
+    const auto fj = h->grow.find(key2(j, j));
+    if (fj == h->grow.end())  // every LMO projects onto itself
+      return h->fail(MBE3_EINVAL, "internal: no gamma rows of (%d,%d)", j, j);
+    // K_(i,j) = Gamma~_(i,i) Gamma~_(j,j)^T (eq. osv_weak_k) of all i of the group
+    GemmTask t = gemm(B_GAMMA, 0, na, 0, B_GAMMA, fj->second * na, na, 1, B_PK, g.k_off, rj,
+                      g.m, rj, na);
+    t.a_rows = (int32_t)rows_k.size();
+    for (int i : g.first) {
+      const auto fi = h->grow.find(key2(i, i));
+      if (fi == h->grow.end())
+        return h->fail(MBE3_EINVAL, "internal: no gamma rows of (%d,%d)", i, i);
+      for (int mu = 0; mu < h->r[i]; ++mu) rows_k.push_back((int32_t)(fi->second + mu));
+      left[i] = 1;
+    }
+    lk.push_back(t);
+    // T_jj X_j (X: d x D, row-major; T_ii the diagonal slot blocks of W), then the
+    // products with X_j and T_jj X_j from the right
+    lbx.push_back(gemm(B_W, h->k_off[j], rj, 0, B_X, h->x_off[j], Dj, 0, B_PP, h->x_off[j], Dj,
+                       rj, Dj, rj));
+    lkx.push_back(gemm(B_PK, g.k_off, rj, 0, B_X, h->x_off[j], Dj, 0, B_PKT, g.t_off, Dj, g.m,
+                       Dj, rj));
+    lsx.push_back(gemm(B_PS2, g.k_off, rj, 0, B_X, h->x_off[j], Dj, 0, B_PDT, 2 * g.t_off,
+                       2 * Dj, g.m, Dj, rj));
+    lsb.push_back(gemm(B_PS2, g.k_off, rj, 0, B_PP, h->x_off[j], Dj, 0, B_PDT,
+                       2 * g.t_off + Dj, 2 * Dj, g.m, Dj, rj));
   }
+  for (int i = 0; i < h->n_occ; ++i)
+    if (left[i])  // T_ii^T X_i
+      ltx.push_back(gemm(B_W, h->k_off[i], h->r[i], 1, B_X, h->x_off[i], h->sD[i], 0, B_PM,
+                         h->x_off[i], h->sD[i], h->r[i], h->sD[i], h->r[i]));
+  weak_S_tasks(h, groups, ls, rows_s);
   int64_t sz[B_COUNT];
   base_sizes(h, sz);
   sz[B_W] = h->k_elems;
-  sz[B_PK] = sz[B_PS2] = sz[B_PM] = ko;
-  sz[B_PP] = po;
-  sz[B_PKT] = sz[B_PDT] = to;
+  sz[B_PK] = sz[B_PS2] = ko;
+  sz[B_PM] = sz[B_PP] = nx;
+  sz[B_PKT] = to;
+  sz[B_PDT] = 2 * to;
   GemmBases b = bases(h);
   b.p[B_GAMMA] = const_cast<double *>(gamma);
   b.p[B_W] = const_cast<double *>(W);
-  b.p[B_PK] = Kb; b.p[B_PS2] = Sb; b.p[B_PM] = Mb; b.p[B_PP] = Pb;
-  b.p[B_PKT] = Kt; b.p[B_PDT] = Dt;
+  b.p[B_PK] = Kb; b.p[B_PS2] = Sb; b.p[B_PM] = TX; b.p[B_PP] = BX;
+  b.p[B_PKT] = KX; b.p[B_PDT] = SX;
   // stream order: each list reads what the ones before it wrote
-  if ((rc = run_call_list(h, tmp, "weak K", lk, sz, b, GEMM_32x32)) ||
-      (rc = run_call_list(h, tmp, "weak S", ls, sz, b, GEMM_32x32)) ||
-      (rc = run_call_list(h, tmp, "weak T S", lm1, sz, b, GEMM_32x32)) ||
-      (rc = run_call_list(h, tmp, "weak S T", lm2, sz, b, GEMM_32x32)) ||
-      (rc = run_call_list(h, tmp, "weak X^T K", lxk, sz, b, GEMM_32x32)) ||
-      (rc = run_call_list(h, tmp, "weak K~", lkx, sz, b, GEMM_32x32)) ||
-      (rc = run_call_list(h, tmp, "weak X^T M", lxm, sz, b, GEMM_32x32)) ||
-      (rc = run_call_list(h, tmp, "weak D~", lmx, sz, b, GEMM_32x32)))
+  if ((rc = run_call_list(h, tmp, "weak K", lk, sz, b, GEMM_128x32, rows_k)) ||
+      (rc = run_call_list(h, tmp, "weak S", ls, sz, b, GEMM_128x32, rows_s)) ||
+      (rc = run_call_list(h, tmp, "weak T^T X", ltx, sz, b, GEMM_32x32)) ||
+      (rc = run_call_list(h, tmp, "weak T X", lbx, sz, b, GEMM_32x32)) ||
+      (rc = run_call_list(h, tmp, "weak K X", lkx, sz, b, GEMM_128x32)) ||
+      (rc = run_call_list(h, tmp, "weak S X", lsx, sz, b, GEMM_128x32)) ||
+      (rc = run_call_list(h, tmp, "weak S T X", lsb, sz, b, GEMM_128x32)))
     return rc;
-  HIP_TRY(h, launch_weak_energy(d_wp, (int)n, Kt, Dt, h->et, h->rank, h->f, h->n_occ, e,
-                                h->stream));
+  HIP_TRY(h, launch_weak_energy(d_wp, (int)n, h->xb, TX, KX, SX, h->et, h->rank, h->f,
+                                h->n_occ, e, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return MBE3_OK;
 }

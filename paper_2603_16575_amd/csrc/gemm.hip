@@ -448,6 +448,7 @@ int gemm_list_form(const GemmTask *ts, int64_t n) {
 
 int gemm_tile_m(GemmShape shape) {
   switch (shape) {
+    case GEMM_128x32:
     case GEMM_128x128: return 128;
     case GEMM_32x32:
     case GEMM_32x128: return 32;
@@ -458,6 +459,7 @@ int gemm_tile_m(GemmShape shape) {
 
 int gemm_tile_n(GemmShape shape) {
   switch (shape) {
+    case GEMM_128x32:
     case GEMM_32x32: return 32;
     case GEMM_64x64: return 64;
     case GEMM_96x96: return 96;
@@ -517,6 +519,7 @@ hipError_t launch_gemm_tasks(const GemmTask *d_tasks, int n_tasks,
     case GEMM_32x128: return launch_shape<32, 128>(d_tasks, n_tasks, grid, bases, form, s);
     case GEMM_64x128: return launch_shape<64, 128>(d_tasks, n_tasks, grid, bases, form, s);
     case GEMM_96x96: return launch_shape<96, 96>(d_tasks, n_tasks, grid, bases, form, s);
+    case GEMM_128x32: return launch_shape<128, 32>(d_tasks, n_tasks, grid, bases, form, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -45,7 +45,12 @@ enum GemmShape {
   GEMM_32x128 = 3,
   GEMM_64x128 = 4,
   GEMM_96x96 = 5,
-  GEMM_NSHAPE = 6
+  GEMM_NSHAPE = 6,  // shapes the tuner chooses from
+  // Not tuned: the lists of weak.hip, one r_j-wide block column over all partners
+  // of LMO j.  12720 pairs of 30 x 30 over 800 and 7376 over 2400 and 800: 2.25 ms
+  // together, 3.8 as a 32x32 task per pair, which read every row block of Q once
+  // per pair and filled one tile each.
+  GEMM_128x32 = 6
 };
 int gemm_tile_m(GemmShape shape);
 int gemm_tile_n(GemmShape shape);
@@ -401,19 +406,22 @@ hipError_t launch_increments(const double *e_frag, const int32_t *sub,
 hipError_t launch_fill(double *p, double v, int64_t n, hipStream_t s);
 
 // ---------------------------------------------------------------------------
-// Pair screening and weak pairs (weak.hip).  Per listed pair (i, j): its
-// r_i x r_j blocks at k_off (S_(i,j), K_(i,j)), its D_i x D_j blocks at t_off
-// (K~, D~) and the offsets of eps~ of the diagonal slots i and j.
+// Pair screening and weak pairs (weak.hip).  The listed pairs are laid out by
+// their second LMO j: its pairs' r_i x r_j blocks S_(i,j), K_(i,j) follow each
+// other as rows of one (sum r_i) x r_j matrix at k_off, K X_j likewise (D_j wide)
+// at t_off, [S X_j, S T_jj X_j] (2 D_j wide) at 2 t_off.
 // ---------------------------------------------------------------------------
 struct WeakPair {
   int32_t i, j, ri, rj, Di, Dj;
-  int64_t k_off, t_off, ei, ej;
+  int64_t k_off, t_off, ei, ej;  // ei, ej: eps~ of the diagonal slots i and j
+  int64_t xi;                    // X_i (and T_ii^T X_i) in the X layout
 };
 hipError_t launch_s2b(const WeakPair *wp, int n, const double *S, double *out,
                       hipStream_t s);
-hipError_t launch_weak_energy(const WeakPair *wp, int n, const double *Kt, const double *Dt,
-                              const double *et, const int32_t *rank, const double *f,
-                              int n_occ, double *e, hipStream_t s);
+hipError_t launch_weak_energy(const WeakPair *wp, int n, const double *X, const double *TX,
+                              const double *KX, const double *SX, const double *et,
+                              const int32_t *rank, const double *f, int n_occ, double *e,
+                              hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 
 }  // namespace mbe3
