@@ -35,8 +35,10 @@
  *   - Every call returns an int status (MBE3_*).  On failure,
  *     mbe3_last_error() describes the cause.  No C++ exception crosses the
  *     ABI.  The library allocates its own device workspace (at create and
- *     on first use); it never frees or writes caller memory other than the
- *     documented outputs.
+ *     on first use); a handle keeps up to 512 MiB of what its allocating
+ *     calls (screen, weak_pairs, project_fit, pair_K_fit, rosv) used for the
+ *     next one, until it is destroyed or an allocation of its own fails.  It
+ *     never frees or writes caller memory other than the documented outputs.
  *   - The handle is not thread safe; concurrent calls on one handle race.
  *
  * Index conventions:
@@ -435,9 +437,9 @@ int mbe3_pm_localize(const double *C, const int32_t *ao_off, int32_t n_ao, int32
  * output (FP64).  W: device, K layout; fragment_solve's multipliers (their
  * diagonal slots are T^MBE_ii), or any caller blocks.  e: device [n].
  * Uses the pair bases of the handle's last eager fragment_solve or
- * mbe3_pair_basis call (prepares them when there was none), allocates and
- * frees its blocks (about 2 sum r_i r_j + 3 sum r_i D_j doubles) inside the call, so it cannot be recorded; synchronises the
- * stream.
+ * mbe3_pair_basis call (prepares them when there was none), allocates its
+ * blocks (about 2 sum r_i r_j + 3 sum r_i D_j doubles) inside the call, so it
+ * cannot be recorded; synchronises the stream.
  * MBE3_EINVAL for a bad pair or argument or while recording.
  */
 int mbe3_weak_pairs(mbe3_handle *h, const int32_t *pairs, int64_t n, const double *gamma,

@@ -51,3 +51,34 @@ def test_weak_groups(m, n_occ, n_vir, n_aux, r):
     sref = np.array([weak.s2b(ora, int(i), int(j)) for i, j in both])
     assert np.abs(s - sref).max() <= 1e-13 * np.abs(sref).max()
     h.close()
+
+
+def test_kept_blocks(m):
+    """Calls whose device blocks the handle keeps give the same bits whatever the
+    calls before left in them: mixed calls of several sizes against the first of
+    their kind on a handle of its own."""
+    import torch
+    prob = synth.micro(n_occ=6, n_vir=70, n_aux=90, r=(9, 20), seed=8)
+    pr = np.array([(i, j) for i in range(6) for j in range(i + 1, 6)], dtype=np.int32)
+
+    def calls(h):
+        gamma = h.osv_project(h.empty_gamma())
+        W = h.pair_K(gamma, h.empty_K())
+        s = h.fit_metric()
+        cut = float(s.median())
+        return [lambda: h.screen(pr), lambda: h.weak_pairs(pr, gamma, W),
+                lambda: h.screen(pr[:2]), lambda: h.project_fit(s, 0.0, h.empty_gamma()),
+                lambda: h.pair_K_fit(s, cut, h.empty_K()), lambda: h.rosv(n_max=30)["Q"],
+                lambda: h.weak_pairs(pr[3:5], gamma, W), lambda: h.project_fit(s, cut, h.empty_gamma()),
+                lambda: h.rosv(n_max=12, s_fit=s, l_fit=cut)["Q"]]
+
+    ref = []
+    for k in range(9):
+        h = m.from_problem(prob, device="cuda:0")
+        ref.append(calls(h)[k]().cpu())
+        h.close()
+    h = m.from_problem(prob, device="cuda:0")
+    c = calls(h)
+    for k in np.random.default_rng(2).integers(0, 9, 40):
+        assert torch.equal(c[k]().cpu(), ref[k]), k
+    h.close()
