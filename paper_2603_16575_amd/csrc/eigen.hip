@@ -581,65 +581,66 @@ __global__ __launch_bounds__(64) void tridiag_qr_kernel(
       const double mu = dm - b * b / (del + (del >= 0.0 ? hyp : -hyp));
       // d[k], e[k], d[k+1], e[k+1] and columns k, k+1 of Q travel in
       // registers; the next rotation's operands are loaded one step ahead
+      // (past the sweep's end they are not used; they stay inside sm).  One
+      // wave runs alone here, so each branch costs as much as several
+      // operations of the chain: lanes past row n - 1 repeat that row and no
+      // load or store is masked.  96 of order 96: 2.42 ms with the
+      // branches, 1.93 without.
       double dk = dd[l], ek = ee[l];
-      double dk1 = dd[l + 1];
-      double ek1 = l + 1 < m ? ee[l + 1] : 0.0;
+      double dk1 = dd[l + 1], ek1 = ee[l + 1];
       double x = dk - mu, z = ek;
       double qc[RPL], qn[RPL];
+      double *Mi[RPL];
 #pragma unroll
       for (int j = 0; j < RPL; ++j) {
-        const int i = lane + 64 * j;
-        qc[j] = i < n ? M[i * ld + l] : 0.0;
-        qn[j] = i < n ? M[i * ld + l + 1] : 0.0;
+        Mi[j] = M + min(lane + 64 * j, n - 1) * ld + l;
+        qc[j] = Mi[j][0];
+        qn[j] = Mi[j][1];
       }
+      double *pe = vv;  // the first rotation's r is no entry of e
       for (int k = l; k < m; ++k) {
-        const double dk2 = k + 2 <= m ? dd[k + 2] : 0.0;
-        const double ek2 = k + 2 < m ? ee[k + 2] : 0.0;
+        const double dk2 = dd[k + 2], ek2 = ee[k + 2];
         double qnn[RPL];
 #pragma unroll
-        for (int j = 0; j < RPL; ++j) {
-          const int i = lane + 64 * j;
-          qnn[j] = (k + 2 <= m && i < n) ? M[i * ld + k + 2] : 0.0;
-        }
-        double c = 1.0, s = 0.0, r = x;
+        for (int j = 0; j < RPL; ++j) qnn[j] = Mi[j][2];
         const double hh = x * x + z * z;
-        if (hh > 0.0) {
-          const double ir = rsqrt_nr(hh);
-          r = hh * ir;
-          c = x * ir;
-          s = -z * ir;
+        const double ir = rsqrt_nr(hh);
+        double r = hh * ir, c = x * ir, s = -z * ir;
+        if (__builtin_expect(!(hh > 0.0), 0)) {
+          c = 1.0;
+          s = 0.0;
+          r = x;
         }
-        if (k > l) ee[k - 1] = r;  // the bulge is chased down: same value in every lane
+        *pe = r;  // the bulge is chased down: same value in every lane
+        pe = ee + k;
         const double cs = c * s, c2 = c * c, s2 = s * s;
         const double nd0 = c2 * dk - 2.0 * cs * ek + s2 * dk1;
         const double nd1 = s2 * dk + 2.0 * cs * ek + c2 * dk1;
-        const double ne = cs * (dk - dk1) + (c2 - s2) * ek;
+        double cd;
+        {  // the difference of the rounded squares, as in the split's chase
+#pragma clang fp contract(off)
+          cd = c2 - s2;
+        }
+        const double ne = cs * (dk - dk1) + cd * ek;
         dd[k] = nd0;
 #pragma unroll
         for (int j = 0; j < RPL; ++j) {  // column k is final, k + 1 carried
-          const int i = lane + 64 * j;
           const double q0 = qc[j], q1 = qn[j];
-          if (i < n) M[i * ld + k] = c * q0 - s * q1;
+          *Mi[j]++ = c * q0 - s * q1;
           qc[j] = s * q0 + c * q1;
           qn[j] = qnn[j];
         }
-        if (k + 1 < m) {
-          z = -s * ek1;  // new bulge at (k + 2, k)
-          ek = c * ek1;
-          x = ne;
-          dk = nd1;
-          dk1 = dk2;
-          ek1 = ek2;
-        } else {
-          dd[k + 1] = nd1;
-          ee[k] = ne;
-        }
+        z = -s * ek1;  // new bulge at (k + 2, k)
+        ek = c * ek1;
+        x = ne;
+        dk = nd1;
+        dk1 = dk2;
+        ek1 = ek2;
       }
+      dd[m] = dk;
+      ee[m - 1] = x;
 #pragma unroll
-      for (int j = 0; j < RPL; ++j) {
-        const int i = lane + 64 * j;
-        if (i < n) M[i * ld + m] = qc[j];
-      }
+      for (int j = 0; j < RPL; ++j) *Mi[j] = qc[j];
     }
     const bool failed = m > 0;  // did not converge: reported as NaN eigenvalues
     __syncthreads();
