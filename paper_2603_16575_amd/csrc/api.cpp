@@ -390,10 +390,46 @@ int64_t finish_tasks(std::vector<GemmTask> &ts, GemmShape shape) {
   return acc;
 }
 
-// Register a task list (tiled for `shape`) with its device copy; *idx gets
-// its index in h->glists.
+// The tile shape a list is planned with: the least of what its tiles cost
+// together, spread over the CUs, and what its dearest tile costs alone (a tile
+// on a CU of its own takes about twice its share).  A tile costs its area times
+// K, padding included, times the shape's cost per multiply-add, measured on
+// products of 800 x 2400 over some 1500 rows (128x128 = 1); filling and draining
+// it counts as further k (2883 products of 80 - 128 cubed: 0.21 ms at 128x128,
+// which has two tiles on a CU, 0.18 at 64x64 and 32x128).  This orders the
+// shapes as measured: S/F blocks of 20 - 40 OSVs 0.91 ms at 32x32, 1.25 at 64x64;
+// pair_K of up to 64 1.34 at 64x64, 1.89 at 32x32; of 66 - 80 1.49 at 96x96, 2.29
+// at 32x32 and 2.77 at 64x64; B^T dGamma 23.8 at 96x96, 24.8 at 128x128; all lists
+// of 13 LMOs 4.6 - 16 us at 32x32, 6 - 26 at 64x64.
+GemmShape planned_shape(const std::vector<GemmTask> &ts) {
+  static const double per_fma[GEMM_NSHAPE] = {1.145, 1.0, 1.615, 1.335, 1.07, 1.015};
+  static const double fill[GEMM_NSHAPE] = {10, 40, 10, 10, 20, 12};
+  static_assert(GEMM_64x64 == 0 && GEMM_128x128 == 1 && GEMM_32x32 == 2 && GEMM_32x128 == 3 &&
+                GEMM_64x128 == 4 && GEMM_96x96 == 5, "per_fma, fill: in the order of GemmShape");
+  int best = 0;
+  double best_cost = 0.0;
+  for (int sh = 0; sh < GEMM_NSHAPE; ++sh) {
+    const GemmShape shape = (GemmShape)sh;
+    const double tile = per_fma[sh] * gemm_tile_m(shape) * gemm_tile_n(shape);
+    double all = 0.0, one = 0.0;
+    for (const GemmTask &t : ts) {
+      const double each = tile * (t.K + fill[sh]);
+      all += each * (double)gemm_tile_count(t, shape);
+      one = std::max(one, each);
+    }
+    const double cost = std::max(all / 256.0, 2.0 * one);
+    if (sh == 0 || cost < best_cost) {
+      best = sh;
+      best_cost = cost;
+    }
+  }
+  return (GemmShape)best;
+}
+
+// Register a task list with its device copy; *idx gets its index in h->glists.
 int add_list(mbe3_handle *h, const std::string &name, std::vector<GemmTask> &ts,
-             GemmShape shape, int rows_table, int *idx) {
+             int rows_table, int *idx) {
+  const GemmShape shape = planned_shape(ts);
   GemmList L;
   L.name = name;
   L.shape = shape;
@@ -408,15 +444,15 @@ int add_list(mbe3_handle *h, const std::string &name, std::vector<GemmTask> &ts,
   return MBE3_OK;
 }
 
-// Register a list as two: tasks whose output is at most 64 wide (planned
-// 64x64 tiles) and the wider ones (planned 96x96), each with its own shape.
+// Register a list as two: tasks whose output is at most 64 wide and the wider
+// ones, each with its own shape.
 int add_split_lists(mbe3_handle *h, const std::string &name, const std::vector<GemmTask> &ts,
                     int *idx_narrow, int *idx_wide) {
   std::vector<GemmTask> nt, wt;
   for (const GemmTask &t : ts) (std::max(t.M, t.N) > 64 ? wt : nt).push_back(t);
   int rc;
-  if (!nt.empty() && (rc = add_list(h, name, nt, GEMM_64x64, 0, idx_narrow))) return rc;
-  if (!wt.empty() && (rc = add_list(h, name + " wide", wt, GEMM_96x96, 0, idx_wide))) return rc;
+  if (!nt.empty() && (rc = add_list(h, name, nt, 0, idx_narrow))) return rc;
+  if (!wt.empty() && (rc = add_list(h, name + " wide", wt, 0, idx_wide))) return rc;
   return MBE3_OK;
 }
 
@@ -675,8 +711,7 @@ int build_plans(mbe3_handle *h) {
     }
     if (!mixed) {  // the split-precision form has its own task lists
       int li = -1;
-      if ((rc = add_list(h, "project " + std::to_string(h->L_proj.size()), ts,
-                         GEMM_128x128, 0, &li)))
+      if ((rc = add_list(h, "project " + std::to_string(h->L_proj.size()), ts, 0, &li)))
         return rc;
       h->L_proj.push_back(li);
     }
@@ -699,10 +734,10 @@ int build_plans(mbe3_handle *h) {
       (d > 64 ? tw : ts).push_back(t);
     }
     if (!mixed_k && !ts.empty() &&
-        (rc = add_list(h, "pair_K", ts, GEMM_64x64, 0, &h->L_pk)))
+        (rc = add_list(h, "pair_K", ts, 0, &h->L_pk)))
       return rc;
     if (!mixed_k && !tw.empty() &&
-        (rc = add_list(h, "pair_K wide", tw, GEMM_96x96, 0, &h->L_pkw)))
+        (rc = add_list(h, "pair_K wide", tw, 0, &h->L_pkw)))
       return rc;
   }
   h->n_rows = (int64_t)rows.size();
@@ -786,7 +821,7 @@ int build_plans(mbe3_handle *h) {
           ts.push_back(gemm(B_Q, h->q_off[x] * nv, nv, 0, B_EQ, h->q_off[y] * nv, nv, 1,
                             B_FS, off, h->r[y], h->r[x], h->r[y], nv));
         }
-    if ((rc = add_list(h, "S/F blocks", ts, GEMM_64x64, 0, &h->L_sf))) return rc;
+    if ((rc = add_list(h, "S/F blocks", ts, 0, &h->L_sf))) return rc;
   }
 
   // ---- pair 4-block S, F (k layout) and the basis pipeline ----
@@ -833,11 +868,11 @@ int build_plans(mbe3_handle *h) {
     h->h_asm.push_back({{B_PS, B_PF}, as});
     h->h_eig.push_back({0, e0});
     h->h_eig.push_back({1, e1});
-    if ((rc = add_list(h, "M1", m1, GEMM_64x64, 0, &h->L_m1))) return rc;
-    if ((rc = add_list(h, "F'", fpt, GEMM_64x64, 0, &h->L_fp))) return rc;
-    if ((rc = add_list(h, "X", xt, GEMM_64x64, 0, &h->L_x))) return rc;
-    if ((rc = add_list(h, "M2", m2, GEMM_64x64, 0, &h->L_m2))) return rc;
-    if ((rc = add_list(h, "K~", ktt, GEMM_64x64, 0, &h->L_kt))) return rc;
+    if ((rc = add_list(h, "M1", m1, 0, &h->L_m1))) return rc;
+    if ((rc = add_list(h, "F'", fpt, 0, &h->L_fp))) return rc;
+    if ((rc = add_list(h, "X", xt, 0, &h->L_x))) return rc;
+    if ((rc = add_list(h, "M2", m2, 0, &h->L_m2))) return rc;
+    if ((rc = add_list(h, "K~", ktt, 0, &h->L_kt))) return rc;
   }
 
   // ---- pair-level S~ between a pair slot and its two diagonal slots ----
@@ -876,8 +911,8 @@ int build_plans(mbe3_handle *h) {
     h->h_asm.push_back({{B_AT, -1}, as});
     if ((rc = upload(h, &h->d_asm_st, as))) return rc;
     if (!gm.empty()) {
-      if ((rc = add_list(h, "S~ M", gm, GEMM_64x64, 0, &h->L_stm))) return rc;
-      if ((rc = add_list(h, "S~", g1, GEMM_64x64, 0, &h->L_st1))) return rc;
+      if ((rc = add_list(h, "S~ M", gm, 0, &h->L_stm))) return rc;
+      if ((rc = add_list(h, "S~", g1, 0, &h->L_st1))) return rc;
     }
     h->at_total = at_total; h->mt_total = mt_total; h->st0_total = st0_total;
     if ((rc = dev_alloc(h, &h->at, at_total))) return rc;
@@ -1703,8 +1738,8 @@ int build_grad_plans(mbe3_handle *h) {
       ww.push_back(gemm(B_TMP, h->x_off[s], D, 0, B_X, h->x_off[s], D, 1, B_W,
                         h->k_off[s], d, d, d, D));
     }
-    if ((rc = add_list(h, "W left", wm, GEMM_64x64, 0, &h->L_wm))) return rc;
-    if ((rc = add_list(h, "W right", ww, GEMM_64x64, 0, &h->L_ww))) return rc;
+    if ((rc = add_list(h, "W left", wm, 0, &h->L_wm))) return rc;
+    if ((rc = add_list(h, "W right", ww, 0, &h->L_ww))) return rc;
   }
   // ---- dGamma~ per destination block (i, x) ----
   std::vector<int32_t> rows;
@@ -1777,8 +1812,8 @@ int build_grad_plans(mbe3_handle *h) {
   }
   h->ga_total = std::max<int64_t>(1, ga_total);
   h->n_ga = (int)segs.size();
-  if ((rc = add_list(h, "dGamma", dg, GEMM_64x64, 1, &h->L_dg))) return rc;
-  if ((rc = add_list(h, "unproject", up, GEMM_128x128, 1, &h->L_up))) return rc;
+  if ((rc = add_list(h, "dGamma", dg, 1, &h->L_dg))) return rc;
+  if ((rc = add_list(h, "unproject", up, 1, &h->L_up))) return rc;
   if ((rc = upload(h, &h->d_ga, segs))) return rc;
   if ((rc = upload(h, &h->d_grows, rows))) return rc;
   h->h_grows = rows;
@@ -2877,8 +2912,8 @@ static int weak_body(mbe3_handle *h, const int32_t *pairs, int64_t n, const doub
   CallList L[7];
   if ((rc = upload_call_list(h, tmp, L[0], "weak K", lk, sz, GEMM_128x32, rows_k)) ||
       (rc = upload_call_list(h, tmp, L[1], "weak S", ls, sz, GEMM_128x32, rows_s)) ||
-      (rc = upload_call_list(h, tmp, L[2], "weak T^T X", ltx, sz, GEMM_32x32)) ||
-      (rc = upload_call_list(h, tmp, L[3], "weak T X", lbx, sz, GEMM_32x32)) ||
+      (rc = upload_call_list(h, tmp, L[2], "weak T^T X", ltx, sz, planned_shape(ltx))) ||
+      (rc = upload_call_list(h, tmp, L[3], "weak T X", lbx, sz, planned_shape(lbx))) ||
       (rc = upload_call_list(h, tmp, L[4], "weak K X", lkx, sz, GEMM_128x32)) ||
       (rc = upload_call_list(h, tmp, L[5], "weak S X", lsx, sz, GEMM_128x32)) ||
       (rc = upload_call_list(h, tmp, L[6], "weak S T X", lsb, sz, GEMM_128x32)))
@@ -3037,8 +3072,9 @@ static int project_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, d
     int64_t *d_out_off = nullptr;
     int32_t *d_rows = nullptr;
     GemmTask *d_ts = nullptr;
-    const int64_t tiles = finish_tasks(ts, GEMM_128x128);
-    if ((rc = check_gemm_list(h, "project (fitting domains)", ts, sz, rows, GEMM_128x128)))
+    const GemmShape shape = planned_shape(ts);
+    const int64_t tiles = finish_tasks(ts, shape);
+    if ((rc = check_gemm_list(h, "project (fitting domains)", ts, sz, rows, shape)))
       return rc;
     if ((rc = tmp.upload(&d_out_off, out_off)) || (rc = tmp.upload(&d_rows, rows)) ||
         (rc = tmp.upload(&d_ts, ts)))
@@ -3053,7 +3089,7 @@ static int project_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, d
     b.p[B_SLAB] = cs;
     b.p[B_GAMMA] = gc;
     b.rows = d_rows;
-    HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, GEMM_128x128,
+    HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, shape,
                                gemm_list_form(ts.data(), (int64_t)ts.size()), s));
   }
   HIP_TRY(h, launch_fit_scatter(gamma, gc, h->gamma_rows, na, max_nc, h->d_row_lmo, d_goff,
@@ -3127,8 +3163,9 @@ static int pair_k_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, do
     int64_t *d_out_off = nullptr;
     int32_t *d_rows = nullptr;
     GemmTask *d_ts = nullptr;
-    const int64_t tiles = finish_tasks(ts, GEMM_64x64);
-    if ((rc = check_gemm_list(h, "project^T (fitting domains)", ts, sz, rows, GEMM_64x64)))
+    const GemmShape shape = planned_shape(ts);
+    const int64_t tiles = finish_tasks(ts, shape);
+    if ((rc = check_gemm_list(h, "project^T (fitting domains)", ts, sz, rows, shape)))
       return rc;
     if ((rc = tmp.upload(&d_out_off, out_off)) || (rc = tmp.upload(&d_rows, rows)) ||
         (rc = tmp.upload(&d_ts, ts)))
@@ -3143,7 +3180,7 @@ static int pair_k_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, do
     b.p[B_SLAB] = cs;
     b.p[B_GAMMA] = gt;
     b.rows = d_rows;
-    HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, GEMM_64x64,
+    HIP_TRY(h, launch_gemm_tasks(d_ts, (int)ts.size(), tiles, b, shape,
                                gemm_list_form(ts.data(), (int64_t)ts.size()), s));
   }
   // K blocks (x, y) of every slot over the union of the two domains
@@ -3207,8 +3244,9 @@ static int pair_k_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, do
   if (!kt.empty()) {
     int32_t *d_krows = nullptr;
     GemmTask *d_kt = nullptr;
-    const int64_t tiles = finish_tasks(kt, GEMM_32x32);
-    if ((rc = check_gemm_list(h, "pair_K (fitting domains)", kt, sz, krows, GEMM_32x32)))
+    const GemmShape shape = planned_shape(kt);
+    const int64_t tiles = finish_tasks(kt, shape);
+    if ((rc = check_gemm_list(h, "pair_K (fitting domains)", kt, sz, krows, shape)))
       return rc;
     if ((rc = tmp.upload(&d_krows, krows)) || (rc = tmp.upload(&d_kt, kt))) return rc;
     PhaseScope ps_(h, MBE3_PHASE_PAIR_K);
@@ -3216,7 +3254,7 @@ static int pair_k_fit_body(mbe3_handle *h, const double *s_fit, double l_fit, do
     b.p[B_GAMMA] = gt;
     b.p[B_K] = K;
     b.rows = d_krows;
-    HIP_TRY(h, launch_gemm_tasks(d_kt, (int)kt.size(), tiles, b, GEMM_32x32,
+    HIP_TRY(h, launch_gemm_tasks(d_kt, (int)kt.size(), tiles, b, shape,
                                gemm_list_form(kt.data(), (int64_t)kt.size()), s));
   }
   return MBE3_OK;
@@ -3355,11 +3393,11 @@ static int rosv_body(mbe3_handle *h, const double *s_fit, double l_fit, double l
     EigTask *d_et = nullptr;
     CallList lT, lY, lTt, lM, lQ;
     if ((rc = tmp.upload(&d_out_off, out_off)) || (rc = tmp.upload(&d_et, et)) ||
-        (rc = upload_call_list(h, tmp, lT, "rosv T", tT, sz, GEMM_128x128)) ||
-        (rc = upload_call_list(h, tmp, lY, "rosv Y", tY, sz, GEMM_64x64)) ||
-        (rc = upload_call_list(h, tmp, lTt, "rosv T~", tTt, sz, GEMM_64x64)) ||
-        (rc = upload_call_list(h, tmp, lM, "rosv M", tM, sz, GEMM_64x64)) ||
-        (rc = upload_call_list(h, tmp, lQ, "rosv Q", tQ, sz, GEMM_64x64)))
+        (rc = upload_call_list(h, tmp, lT, "rosv T", tT, sz, planned_shape(tT))) ||
+        (rc = upload_call_list(h, tmp, lY, "rosv Y", tY, sz, planned_shape(tY))) ||
+        (rc = upload_call_list(h, tmp, lTt, "rosv T~", tTt, sz, planned_shape(tTt))) ||
+        (rc = upload_call_list(h, tmp, lM, "rosv M", tM, sz, planned_shape(tM))) ||
+        (rc = upload_call_list(h, tmp, lQ, "rosv Q", tQ, sz, planned_shape(tQ))))
       return rc;
     HIP_TRY(h, launch_fill(T, 0.0, (int64_t)nb * t_elems, st));  // LMOs with empty domains
     HIP_TRY(h, launch_regen_cols(cs, d_out_off, d_cols, d_col_off, i0, nb, cs_per, nv, na,
