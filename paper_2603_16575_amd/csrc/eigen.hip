@@ -1295,55 +1295,51 @@ hipError_t launch_eigh_split(const EigTask *d_tasks, int n_tasks, int max_n,
                              double *gws, int64_t gws_doubles, hipStream_t s) {
   if (n_tasks <= 0) return hipSuccess;
   if (!cws || !meta || !redo) return hipErrorInvalidValue;
-  hipError_t e = hipSuccess;
   const int top = std::min(max_n, SPLIT_MAX_ORDER);
+  // House and apply go by ranges of 64 orders, each with the LDS of its own; the
+  // split launches select tasks by their order rank[slot] (order 0, an empty
+  // basis, in the first range).  The chase, whose LDS does not depend on the
+  // order, takes all at once: it is a chain per matrix that leaves most of the
+  // chip idle, so ranges one after the other cost the sum of their longest chains
+  // (5504 matrices up to order 80: 5.2 ms in two launches, 3.0 in one).
+  hipError_t e = hipFuncSetAttribute((const void *)tridiag_house_kernel,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)qr_smem(top));
   for (int lo = 1; lo <= top && e == hipSuccess; lo += 64) {
     const int hi = std::min(top, lo + 63);
-    // the split launches select tasks by their order rank[slot] (order 0,
-    // an empty basis, in the first range); the fused fallback by t.n, the
-    // range whose LDS it reserved: each task's redo flag is written by the
-    // apply launch of its order's range, before the fallback of t.n's
-    const int rlo = lo == 1 ? 0 : lo;
-    const size_t hs = qr_smem(hi);
+    hipLaunchKernelGGL(tridiag_house_kernel, dim3(n_tasks), dim3(256), qr_smem(hi), s, d_tasks,
+                       n_tasks, in, out, rank, cws, lo == 1 ? 0 : lo, hi);
+    e = hipGetLastError();
+  }
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(tridiag_chase_kernel, dim3(n_tasks), dim3(64), 0, s, d_tasks, n_tasks, rank,
+                     cws, meta, 0, top);
+  e = hipGetLastError();
+  int smem = 0;
+  for (int lo = 1; lo <= top && e == hipSuccess; lo += 64) {
+    const int hi = std::min(top, lo + 63);
     // 512 staged rotations (8 KB) keep the record's reads off the chain;
     // more would only take LDS from other workgroups
     int stage = (int)std::min<int64_t>(512, ((int64_t)EIG_LDS - (int64_t)apply_smem(hi, 0)) / 16);
     stage = stage / 64 * 64;
     if (stage < 64) return hipErrorInvalidValue;
-    const size_t as = apply_smem(hi, stage);
-    if (hi <= 64) {
-      e = hipFuncSetAttribute((const void *)tridiag_house_kernel,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)hs);
-      if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)tridiag_apply_kernel,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)as);
+    const int as = (int)apply_smem(hi, stage);
+    if (as > smem) {
+      smem = as;
+      e = hipFuncSetAttribute((const void *)tridiag_apply_kernel,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, smem);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(tridiag_house_kernel, dim3(n_tasks), dim3(256), hs, s, d_tasks,
-                         n_tasks, in, out, rank, cws, rlo, hi);
-      hipLaunchKernelGGL(tridiag_chase_kernel, dim3(n_tasks), dim3(64), 0, s, d_tasks,
-                         n_tasks, rank, cws, meta, rlo, hi);
-      hipLaunchKernelGGL(tridiag_apply_kernel, dim3(n_tasks), dim3(256), as, s, d_tasks,
-                         n_tasks, rank, cws, meta, out, evals, redo, stage, rlo, hi);
-      e = hipGetLastError();
-      if (e == hipSuccess)  // records that overflowed: the fused kernel
-        e = launch_qr<1>(d_tasks, n_tasks, lo, hi, in, out, evals, rank, 1, 0.0, redo, s);
-    } else {
-      e = hipFuncSetAttribute((const void *)tridiag_house_kernel,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)hs);
-      if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)tridiag_apply_kernel,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)as);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(tridiag_house_kernel, dim3(n_tasks), dim3(256), hs, s, d_tasks,
-                         n_tasks, in, out, rank, cws, rlo, hi);
-      hipLaunchKernelGGL(tridiag_chase_kernel, dim3(n_tasks), dim3(64), 0, s, d_tasks,
-                         n_tasks, rank, cws, meta, rlo, hi);
-      hipLaunchKernelGGL(tridiag_apply_kernel, dim3(n_tasks), dim3(256), as, s, d_tasks,
-                         n_tasks, rank, cws, meta, out, evals, redo, stage, rlo, hi);
-      e = hipGetLastError();
-      if (e == hipSuccess)
-        e = launch_qr<2>(d_tasks, n_tasks, lo, hi, in, out, evals, rank, 1, 0.0, redo, s);
     }
+    hipLaunchKernelGGL(tridiag_apply_kernel, dim3(n_tasks), dim3(256), as, s, d_tasks, n_tasks,
+                       rank, cws, meta, out, evals, redo, stage, lo == 1 ? 0 : lo, hi);
+    e = hipGetLastError();
+  }
+  // records that overflowed: the fused kernel, selected by t.n, the range whose
+  // LDS it reserves
+  for (int lo = 1; lo <= top && e == hipSuccess; lo += 64) {
+    const int hi = std::min(top, lo + 63);
+    e = hi <= 64 ? launch_qr<1>(d_tasks, n_tasks, lo, hi, in, out, evals, rank, 1, 0.0, redo, s)
+                 : launch_qr<2>(d_tasks, n_tasks, lo, hi, in, out, evals, rank, 1, 0.0, redo, s);
   }
   if (e != hipSuccess || max_n <= SPLIT_MAX_ORDER) return e;
   // orders above the split path: the fused kernel, then cyclic Jacobi
