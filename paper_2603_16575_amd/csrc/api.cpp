@@ -406,18 +406,23 @@ GemmShape planned_shape(const std::vector<GemmTask> &ts) {
   static const double fill[GEMM_NSHAPE] = {10, 40, 10, 10, 20, 12};
   static_assert(GEMM_64x64 == 0 && GEMM_128x128 == 1 && GEMM_32x32 == 2 && GEMM_32x128 == 3 &&
                 GEMM_64x128 == 4 && GEMM_96x96 == 5, "per_fma, fill: in the order of GemmShape");
+  double all[GEMM_NSHAPE] = {};
+  int k_max = 0;
+  for (const GemmTask &t : ts) {
+    const int64_t m = (t.M + 31) / 32, n = (t.N + 31) / 32;  // in 32s, then by tile side
+    const int64_t m64 = (m + 1) / 2, m96 = (m + 2) / 3, m128 = (m + 3) / 4;
+    const int64_t n64 = (n + 1) / 2, n96 = (n + 2) / 3, n128 = (n + 3) / 4;
+    const int64_t tiles[GEMM_NSHAPE] = {m64 * n64, m128 * n128, m * n,
+                                        m * n128,  m64 * n128,  m96 * n96};
+    for (int sh = 0; sh < GEMM_NSHAPE; ++sh) all[sh] += (double)tiles[sh] * (t.K + fill[sh]);
+    k_max = std::max(k_max, (int)t.K);
+  }
   int best = 0;
   double best_cost = 0.0;
   for (int sh = 0; sh < GEMM_NSHAPE; ++sh) {
-    const GemmShape shape = (GemmShape)sh;
-    const double tile = per_fma[sh] * gemm_tile_m(shape) * gemm_tile_n(shape);
-    double all = 0.0, one = 0.0;
-    for (const GemmTask &t : ts) {
-      const double each = tile * (t.K + fill[sh]);
-      all += each * (double)gemm_tile_count(t, shape);
-      one = std::max(one, each);
-    }
-    const double cost = std::max(all / 256.0, 2.0 * one);
+    const double tile =
+        per_fma[sh] * gemm_tile_m((GemmShape)sh) * gemm_tile_n((GemmShape)sh);
+    const double cost = tile * std::max(all[sh] / 256.0, 2.0 * (k_max + fill[sh]));
     if (sh == 0 || cost < best_cost) {
       best = sh;
       best_cost = cost;

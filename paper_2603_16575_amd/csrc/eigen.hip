@@ -389,6 +389,38 @@ __device__ inline double rsqrt_nr(double h) {
   return y;
 }
 
+// One rotation of an implicit QR sweep: the entry x and the bulge z under it
+// become (r, 0), rows k and k + 1 [dk, ek; ek, dk1] are turned (dk's new value to
+// d_out), and ek1, the entry below, gives the next bulge and off-diagonal.
+// A sweep runs on one wave, which issues an FP64 operation every 5.5 clocks
+// (7 if it waits for the one before) and every other instruction in about as
+// many: what costs is the number of instructions, so the loops around it have
+// their loads unconditional, one step ahead, and are unrolled until copies and
+// addresses fold away.
+struct Rotation {
+  double c, s, r;
+};
+__device__ __forceinline__ Rotation qr_rotation(double &x, double &z, double &dk, double &ek,
+                                                double dk1, double ek1, double &d_out) {
+  const double hh = x * x + z * z;
+  const double ir = rsqrt_nr(hh);
+  Rotation o{x * ir, -z * ir, hh * ir};
+  if (__builtin_expect(!(hh > 0.0), 0)) o = Rotation{1.0, 0.0, x};
+  const double cs = o.c * o.s, c2 = o.c * o.c, s2 = o.s * o.s;
+  double cd;
+  {  // the difference of the rounded squares
+#pragma clang fp contract(off)
+    cd = c2 - s2;
+  }
+  d_out = c2 * dk - 2.0 * cs * ek + s2 * dk1;
+  const double nd1 = s2 * dk + 2.0 * cs * ek + c2 * dk1;
+  x = cs * (dk - dk1) + cd * ek;
+  z = -o.s * ek1;
+  ek = o.c * ek1;
+  dk = nd1;
+  return o;
+}
+
 template <int RPL>
 __global__ __launch_bounds__(64) void tridiag_qr_kernel(
     const EigTask *__restrict__ tasks, int n_tasks, const double *__restrict__ in,
@@ -581,11 +613,9 @@ __global__ __launch_bounds__(64) void tridiag_qr_kernel(
       const double mu = dm - b * b / (del + (del >= 0.0 ? hyp : -hyp));
       // d[k], e[k], d[k+1], e[k+1] and columns k, k+1 of Q travel in
       // registers; the next rotation's operands are loaded one step ahead
-      // (past the sweep's end they are not used; they stay inside sm).  One
-      // wave runs alone here, so each branch costs as much as several
-      // operations of the chain: lanes past row n - 1 repeat that row and no
-      // load or store is masked.  96 of order 96: 2.42 ms with the
-      // branches, 1.93 without.
+      // (past the sweep's end they are not used; they stay inside sm).  Lanes
+      // past row n - 1 repeat that row, so no load or store is masked.  96 of
+      // order 96: 2.42 ms with branches and masks, 1.93 without, 1.66 unrolled.
       double dk = dd[l], ek = ee[l];
       double dk1 = dd[l + 1], ek1 = ee[l + 1];
       double x = dk - mu, z = ek;
@@ -598,42 +628,22 @@ __global__ __launch_bounds__(64) void tridiag_qr_kernel(
         qn[j] = Mi[j][1];
       }
       double *pe = vv;  // the first rotation's r is no entry of e
+#pragma unroll 4
       for (int k = l; k < m; ++k) {
         const double dk2 = dd[k + 2], ek2 = ee[k + 2];
         double qnn[RPL];
 #pragma unroll
         for (int j = 0; j < RPL; ++j) qnn[j] = Mi[j][2];
-        const double hh = x * x + z * z;
-        const double ir = rsqrt_nr(hh);
-        double r = hh * ir, c = x * ir, s = -z * ir;
-        if (__builtin_expect(!(hh > 0.0), 0)) {
-          c = 1.0;
-          s = 0.0;
-          r = x;
-        }
-        *pe = r;  // the bulge is chased down: same value in every lane
+        const Rotation o = qr_rotation(x, z, dk, ek, dk1, ek1, dd[k]);
+        *pe = o.r;  // the bulge is chased down: same value in every lane
         pe = ee + k;
-        const double cs = c * s, c2 = c * c, s2 = s * s;
-        const double nd0 = c2 * dk - 2.0 * cs * ek + s2 * dk1;
-        const double nd1 = s2 * dk + 2.0 * cs * ek + c2 * dk1;
-        double cd;
-        {  // the difference of the rounded squares, as in the split's chase
-#pragma clang fp contract(off)
-          cd = c2 - s2;
-        }
-        const double ne = cs * (dk - dk1) + cd * ek;
-        dd[k] = nd0;
 #pragma unroll
         for (int j = 0; j < RPL; ++j) {  // column k is final, k + 1 carried
           const double q0 = qc[j], q1 = qn[j];
-          *Mi[j]++ = c * q0 - s * q1;
-          qc[j] = s * q0 + c * q1;
+          *Mi[j]++ = o.c * q0 - o.s * q1;
+          qc[j] = o.s * q0 + o.c * q1;
           qn[j] = qnn[j];
         }
-        z = -s * ek1;  // new bulge at (k + 2, k)
-        ek = c * ek1;
-        x = ne;
-        dk = nd1;
         dk1 = dk2;
         ek1 = ek2;
       }
@@ -913,7 +923,8 @@ __global__ __launch_bounds__(256) void tridiag_house_kernel(
 __global__ __launch_bounds__(64) void tridiag_chase_kernel(
     const EigTask *__restrict__ tasks, int n_tasks, const int32_t *__restrict__ rank,
     double *__restrict__ cws, int32_t *__restrict__ meta, int n_lo, int n_hi) {
-  __shared__ double dd[SPLIT_MAX_ORDER + 1], ee[SPLIT_MAX_ORDER + 1];
+  // read up to two entries past the order, and one for an r that is no entry
+  __shared__ double dd[SPLIT_MAX_ORDER + 2], ee[SPLIT_MAX_ORDER + 3];
   constexpr int RPL = (SPLIT_MAX_ORDER + 63) / 64;
   const int lane = threadIdx.x;
   for (int ti = blockIdx.x; ti < n_tasks; ti += gridDim.x) {
@@ -960,63 +971,47 @@ __global__ __launch_bounds__(64) void tridiag_chase_kernel(
         ovf = 1;
         break;
       }
+      // one lane: the chain is serial, and its stores to the record need no mask.
+      // 5504 matrices up to order 80: 3.0 ms with branches, masks and copies in
+      // the loop, 2.2 without.
       if (lane == 0) {
         bounds[2 * ns] = l;
         bounds[2 * ns + 1] = m;
-        for (int k = bl; k < l; ++k) {
-          rot[2 * (nr + k - bl)] = 1.0;
-          rot[2 * (nr + k - bl) + 1] = 0.0;
+        double *rc = rot + 2 * nr;
+        for (int k = bl; k < l; ++k, rc += 2) {
+          rc[0] = 1.0;
+          rc[1] = 0.0;
         }
-        for (int k = m; k < bm; ++k) {
-          rot[2 * (nr + k - bl)] = 1.0;
-          rot[2 * (nr + k - bl) + 1] = 0.0;
+        const double dm1 = dd[m - 1], dm = dd[m], b = ee[m - 1];
+        const double del = 0.5 * (dm1 - dm);
+        const double hyp = sqrt(del * del + b * b);
+        const double mu = dm - b * b / (del + (del >= 0.0 ? hyp : -hyp));
+        double dk = dd[l], ek = ee[l];
+        double dk1 = dd[l + 1], ek1 = ee[l + 1];
+        double x = dk - mu, z = ek;
+        double *pe = ee + SPLIT_MAX_ORDER + 2;
+#pragma unroll 4
+        for (int k = l; k < m; ++k) {
+          const double dk2 = dd[k + 2], ek2 = ee[k + 2];
+          const Rotation o = qr_rotation(x, z, dk, ek, dk1, ek1, dd[k]);
+          *pe = o.r;
+          pe = ee + k;
+          rc[0] = o.c;
+          rc[1] = o.s;
+          rc += 2;
+          dk1 = dk2;
+          ek1 = ek2;
+        }
+        dd[m] = dk;
+        ee[m - 1] = x;
+        for (int k = m; k < bm; ++k, rc += 2) {
+          rc[0] = 1.0;
+          rc[1] = 0.0;
         }
       }
       ++ns;
-      nr += l - bl;  // the sweep's own rotations follow its leading pad
-      const double dm1 = dd[m - 1], dm = dd[m], b = ee[m - 1];
-      const double del = 0.5 * (dm1 - dm);
-      const double hyp = sqrt(del * del + b * b);
-      const double mu = dm - b * b / (del + (del >= 0.0 ? hyp : -hyp));
-      double dk = dd[l], ek = ee[l];
-      double dk1 = dd[l + 1];
-      double ek1 = l + 1 < m ? ee[l + 1] : 0.0;
-      double x = dk - mu, z = ek;
-      for (int k = l; k < m; ++k) {
-        const double dk2 = k + 2 <= m ? dd[k + 2] : 0.0;
-        const double ek2 = k + 2 < m ? ee[k + 2] : 0.0;
-        double c = 1.0, s = 0.0, r = x;
-        const double hh = x * x + z * z;
-        if (hh > 0.0) {
-          const double ir = rsqrt_nr(hh);
-          r = hh * ir;
-          c = x * ir;
-          s = -z * ir;
-        }
-        if (k > l) ee[k - 1] = r;
-        const double cs = c * s, c2 = c * c, s2 = s * s;
-        const double nd0 = c2 * dk - 2.0 * cs * ek + s2 * dk1;
-        const double nd1 = s2 * dk + 2.0 * cs * ek + c2 * dk1;
-        const double ne = cs * (dk - dk1) + (c2 - s2) * ek;
-        dd[k] = nd0;
-        if (lane == 0) {
-          rot[2 * nr] = c;
-          rot[2 * nr + 1] = s;
-        }
-        ++nr;
-        if (k + 1 < m) {
-          z = -s * ek1;
-          ek = c * ek1;
-          x = ne;
-          dk = nd1;
-          dk1 = dk2;
-          ek1 = ek2;
-        } else {
-          dd[k + 1] = nd1;
-          ee[k] = ne;
-        }
-      }
-      nr += ((m - 1) | 15) + 1 - m;  // the trailing pad
+      nr += bm - bl;
+      __syncthreads();
     }
     __syncthreads();
     for (int i = lane; i < n; i += 64) rec[i] = dd[i];  // the eigenvalues, unsorted
