@@ -1700,7 +1700,7 @@ int build_grad_plans(mbe3_handle *h) {
         w.e_end = (int32_t)we.size();
         ws.push_back(w);
       }
-      // bounds: W~ block of the slot, each entry's Y~ block in the store
+      // bounds: W~ block of the slot, each entry's Y block in the store
       if (h->kt_off[kv.first] + nel > h->kt_off[h->n_slot]) return bad("W~ slot", kv.first);
       for (const WEntry &e : kv.second)
         if (e.yoff < 0 || e.yoff + nel > ch.ny_total) return bad("W~ entry", kv.first);
