@@ -1987,8 +1987,9 @@ static int weak_layout(mbe3_handle *h, const int32_t *pairs, int64_t n, bool ord
     g.m += w.ri;
     g.first.push_back(i);
   }
-  int64_t ko = 0, to = 0;
+  int64_t ko = 0, to = 0, rows = 0;
   for (WeakGroup &g : groups) {
+    rows += g.m;
     g.k_off = ko;
     g.t_off = to;
     ko += (int64_t)g.m * h->r[g.j];
@@ -2002,6 +2003,8 @@ static int weak_layout(mbe3_handle *h, const int32_t *pairs, int64_t n, bool ord
     w.t_off = g.t_off + row * w.Dj;
   }
   *k_tot = ko; *t_tot = to;
+  if (rows > 0x7fffffffLL)  // the row tables are indexed by 32 bits
+    return h->fail(MBE3_EINVAL, "too many pairs (%lld rows)", (long long)rows);
   return MBE3_OK;
 }
 
