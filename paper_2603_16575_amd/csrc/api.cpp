@@ -1194,6 +1194,7 @@ int build_plans(mbe3_handle *h) {
     si[s].d = h->sd[s]; si[s].D = h->sD[s];
     si[s].kt_off = h->kt_off[s]; si[s].et_off = h->et_off[s];
     si[s].base_off = h->base_off[s];
+    si[s].unsym = si[s].pad_ = 0;
   }
   if ((rc = upload(h, &h->d_slots, si))) return rc;
   if ((rc = upload(h, &h->d_coef, h->coef))) return rc;
@@ -2521,7 +2522,7 @@ int fragment_solve(mbe3_handle *h, const double *K, double *e_frag,
   if (W && (rc = no_throw(h, [&] { return build_grad_plans(h); }))) return rc;
   if ((rc = prepare_pairs(h, K))) return rc;
   GemmBases b = bases(h);
-  HIP_TRY(h, launch_fill_i32(h->status, 0, 2 * SOLVE_WG, s));
+  HIP_TRY(h, launch_solve_begin(h->d_slots, h->kt, h->n_occ, h->status, 2 * SOLVE_WG, s));
   if (W) {
     PhaseScope ps_(h, MBE3_PHASE_GRAD);
     HIP_TRY(h, launch_fill(h->wt, 0.0, h->kt_off[h->n_slot], s));

@@ -255,6 +255,7 @@ struct SlotInfo {
   int64_t et_off;    // eps~ (D) in the eps~ store
   int64_t base_off;  // pair slots: coupling sums of the pair's own fragment
                      // (D_p^2, D_q^2, D^2 doubles), or -1
+  int32_t unsym, pad_;  // diagonal slots: K~ is not symmetric (launch_solve_begin)
 };
 struct FragDesc {
   int32_t nt;           // number of pair slots (1, 3 or 6)
@@ -316,6 +317,10 @@ struct SolveArgs {
   double *gterm;
   double *gdiag;
 };
+// Before a step's first launch_solve: clears status[n_status] and sets the diagonal
+// slots' unsym from their K~.
+hipError_t launch_solve_begin(SlotInfo *slots, const double *kt, int n_occ, int32_t *status,
+                              int n_status, hipStream_t s);
 hipError_t launch_solve(const SolveArgs &a, int n_wg, hipStream_t s);
 // Coupling sums of a chunk's dimers at the warm store's amplitudes, for the
 // first sweep of the trimers that contain them.
@@ -422,6 +427,5 @@ hipError_t launch_weak_energy(const WeakPair *wp, int n, const double *X, const 
                               const double *KX, const double *SX, const double *et,
                               const int32_t *rank, const double *f, int n_occ, double *e,
                               hipStream_t s);
-hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 
 }  // namespace mbe3

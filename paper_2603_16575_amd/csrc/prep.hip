@@ -79,18 +79,4 @@ hipError_t launch_fill(double *p, double v, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void fill_i32_kernel(int32_t *p, int32_t v, int64_t n) {
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x)
-    p[e] = v;
-}
-
-hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, v, n);
-  return hipGetLastError();
-}
-
 }  // namespace mbe3

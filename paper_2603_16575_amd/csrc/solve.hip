@@ -85,8 +85,9 @@ struct TermLds {
 };
 struct SlotLds {
   int64_t kt_off, et_off;
+  const double *gy;  // gradient pass: the amplitudes its terms read
   double fpq;  // f_pp + f_qq
-  int32_t D, ysub, sym, wgt;
+  int32_t D, ysub, sym, wgt;  // sym: 1 diagonal, 2 diagonal with an unsymmetric K~
   int32_t tb, tx, te;  // the slot's terms of this launch in tc[], the first
                        // of them that couples two pairs of a trimer
   int64_t b0, b1;      // coupling sums of the slot (second one: diagonal
@@ -220,12 +221,12 @@ __device__ __forceinline__ uint32_t part_mask(int part, int lg, int n) {
 // fragments: the terms [tb, tg) of each pair target are formed once more from
 // the stored Y with unit coefficient and contracted with Y~ = 2Y - Y^T.  The
 // coupling operator is symmetric, so a term's contraction equals its mirror's
-// (source and target exchanged) up to the pair weights, and 9 of a trimer's 18
-// terms are enough; of each couple the one with the wider target runs, which
-// leaves fewer waves without a row block.  Measured at 160 orbitals (90k
-// fragments): 29.8 ms for 59.8 ms with every term.  Fragments that did not
-// converge (iters < 0) are skipped.  Keeping the pass out of the solving launch
-// keeps its registers out of the iterations.
+// (source and target exchanged) up to the pair weights (an unsymmetric diagonal
+// source is adapted to that), and 9 of a trimer's 18 terms are enough; of each
+// couple the one with the wider target runs, which leaves fewer waves without a
+// row block.  Measured at 160 orbitals (90k fragments): 28.4 ms for 59.8 ms with
+// every term.  Fragments that did not converge (iters < 0) are skipped.  Keeping
+// the pass out of the solving launch keeps its registers out of the iterations.
 template <int MAXNT, int MODE, int NW>
 __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void solve_kernel(SolveArgs a) {
   constexpr bool ST = MODE == 1, GP = MODE == 2, BASE = MODE == 3;
@@ -289,11 +290,12 @@ __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void sol
       c.fpq = a.f_occ[(int64_t)sl.p * a.n_occ + sl.p] + a.f_occ[(int64_t)sl.q * a.n_occ + sl.q];
       c.D = sl.D;
       c.ysub = fdp->ysub[tl];
-      c.sym = fdp->sym[tl];
+      c.sym = fdp->sym[tl] ? 1 + sl.unsym : 0;
       c.wgt = fdp->wgt[tl];
       c.tb = fdp->tb[tl];
       c.tx = fdp->tx[tl];
       c.te = GP ? fdp->tg[tl] : fdp->te[tl];
+      c.gy = !GP ? nullptr : (c.sym == 2 ? Y0 : a.yfin + fdp->yout) + c.ysub;
       c.b0 = c.b1 = 0;
       if (BASE) {
         c.b0 = base_of(a.slots, a.slots[fdp->slot[2]], tl);
@@ -311,21 +313,35 @@ __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void sol
     if (GP) {
       // the pass reads the stored Y in place; the contraction weights 2Y -
       // Y^T = Y~ of the pair targets go to the second scratch buffer, and
-      // <Y~_t, Y_t> to gdiag
+      // <Y~_t, Y_t> to gdiag.  A term with a diagonal source p stands for itself,
+      // 2 <Y~_t, Z(Y_p)>, and for its mirror, <Y_p + Y_p^T, Z^T(Y_t)> = <Y_t +
+      // Y_t^T, Z(Y_p)>: together 4 <Y~_t, Z((3 Y_p + Y_p^T) / 4)>, which differs
+      // from 4 <Y~_t, Z(Y_p)> where Y_p is not symmetric; such a source is read
+      // from the first scratch buffer
       for (int tl = 0; tl < f_nt; ++tl) {
         const int D = sc[tl].D;
         const int sy = sc[tl].sym;
         const double *y = a.yfin + fdp->yout + sc[tl].ysub;
-        double *wy = Y0 + ny_cap + sc[tl].ysub;
+        double *out = Y0 + (sy ? 0 : ny_cap) + sc[tl].ysub;
+        const double ca = sy ? 0.75 : 2.0, cb = sy ? 0.25 : -1.0;
         double part = 0.0;
-        for (int e = tid; e < D * D; e += NTH) {
-          const int i = e / D, j = e - i * D;
-          const double yv = y[e], yt = y[(int64_t)j * D + i];
-          const double ytil = 2.0 * yv - yt;
-          if (!sy) wy[e] = ytil;
-          part += ytil * yv;
+        for (int e0 = tid; e0 < D * D; e0 += 4 * NTH) {
+          double yv[4], yt[4];  // eight loads in flight
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * NTH < D * D ? e0 + u * NTH : e0;
+            const int i = e / D, j = e - i * D;
+            yv[u] = y[e];
+            yt[u] = y[j * D + i];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (e0 + u * NTH < D * D) {
+              if (sy != 1) out[e0 + u * NTH] = ca * yv[u] + cb * yt[u];
+              part += (2.0 * yv[u] - yt[u]) * yv[u];
+            }
         }
-        const double tot = wg_sum<NW>(part, red_d);  // also orders the wy writes
+        const double tot = wg_sum<NW>(part, red_d);  // also orders these writes
         if (tid == 0) a.gdiag[6 * fi + tl] = tot;
       }
       hasY = true;
@@ -338,13 +354,14 @@ __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void sol
     for (int it = 0;; ++it) {
       double mres = 0.0, epart = 0.0;
       int bad = 0;
-      double *const Ycb = GP ? a.yfin + fdp->yout : Y0 + (cur ? ny_cap : 0);
+      double *const Ycb = Y0 + (cur ? ny_cap : 0);
       double *const Ynb = Y0 + (cur ? 0 : ny_cap);
       // a warm-started trimer's first sweep: the terms within its pairs' own
       // fragments are summed already
       const bool bsrc = !BASE && !GP && wsrc && a.base;
       // the current amplitudes of target / source slot tl
       auto ysrc = [&](int tl) -> const double * {
+        if (GP) return sc[tl].gy;
         return wsrc ? a.warm + sc[tl].kt_off : Ycb + sc[tl].ysub;
       };
 
@@ -513,14 +530,17 @@ __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void sol
             }
             if (GP) {
               // this term's product alone, contracted with Y~ = 2Y - Y^T
-              const double *Wy = Y0 + ny_cap + sl.ysub;
+              const double *Wy = uniform((const double *)(Y0 + ny_cap + sl.ysub));
               double part = 0.0;
 #pragma unroll
               for (int jb = 0; jb < MAXNT; ++jb) {
                 if (cnt > 0 && jb < nT) {
+                  d4 wy;  // four loads in flight (one by one: a sixth of the pass)
 #pragma unroll
                   for (int v = 0; v < 4; ++v)
-                    part += Wy[(rp.ib * 16 + lq + 4 * v) * Dt + jb * 16 + l16] * acc[jb][v];
+                    wy[v] = at(Wy, (rp.ib * 16 + lq + 4 * v) * Dt + jb * 16 + l16);
+#pragma unroll
+                  for (int v = 0; v < 4; ++v) part += wy[v] * acc[jb][v];
                 }
                 acc[jb] = d4{0.0, 0.0, 0.0, 0.0};
               }
@@ -529,7 +549,7 @@ __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void sol
                 for (int jb = 0; jb < NR2; ++jb) {
 #pragma unroll
                   for (int v = 0; v < 4; ++v)
-                    part += Wy[(64 + lq + 4 * v) * Dt + jb * 16 + l16] * acc2[jb][v];
+                    part += at(Wy, (64 + lq + 4 * v) * Dt + jb * 16 + l16) * acc2[jb][v];
                   acc2[jb] = d4{0.0, 0.0, 0.0, 0.0};
                 }
               }
@@ -616,7 +636,8 @@ __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void sol
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
             const int ij = (i0 + 4 * v) * Dt + j;
-            const int ji = sym ? ij : j * Dt + i0 + 4 * v;  // Y_pp is symmetric
+            // Y_pp is symmetric where K~_pp is (its other terms are made so)
+            const int ji = sym == 1 ? ij : j * Dt + i0 + 4 * v;
             f.k[v] = at(Kt, ij);
             f.y[v] = at(Yq, ij);
             f.yt[v] = at(Yq, ji);
@@ -738,6 +759,56 @@ __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void sol
       cur ^= 1;
     }
   }
+}
+
+// Cleared status words, and SlotInfo::unsym: whether K~_pp is unsymmetric (1) or
+// symmetric to 2^-36 of its largest element (0): what that leaves of <Y - Y^T, K~>
+// is below the rounding of the energy (a NaN ends the fragment anyway).  pair_K's
+// blocks are symmetric to rounding, and their transposed Y need not be read: 148.8 ms
+// instead of 149.9 for the 160-orbital step, 166.2 instead of 168.7 for 96 orbitals
+// of 24 - 64 OSVs.
+__global__ __launch_bounds__(1024) void solve_begin_kernel(SlotInfo *__restrict__ slots,
+                                                           const double *__restrict__ kt,
+                                                           int n_occ,
+                                                           int32_t *__restrict__ status,
+                                                           int n_status) {
+  if ((int)blockIdx.x == n_occ) {
+    for (int k = threadIdx.x; k < n_status; k += 1024) status[k] = 0;
+    return;
+  }
+  __shared__ double big[16], dif[16];
+  const SlotInfo sl = slots[blockIdx.x];
+  const double *K = kt + sl.kt_off;
+  double b = 0.0, d = 0.0;
+  for (int e = threadIdx.x; e < sl.D * sl.D; e += 1024) {
+    const int i = e / sl.D, j = e - i * sl.D;
+    const double x = K[e], y = K[j * sl.D + i];
+    b = fmax(b, fabs(x));
+    d = fmax(d, fabs(x - y));
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    b = fmax(b, __shfl_xor(b, o));
+    d = fmax(d, __shfl_xor(d, o));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    big[threadIdx.x >> 6] = b;
+    dif[threadIdx.x >> 6] = d;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) {
+      b = fmax(b, big[w]);
+      d = fmax(d, dif[w]);
+    }
+    slots[blockIdx.x].unsym = d <= 0x1p-36 * b ? 0 : 1;
+  }
+}
+
+hipError_t launch_solve_begin(SlotInfo *slots, const double *kt, int n_occ, int32_t *status,
+                              int n_status, hipStream_t s) {
+  hipLaunchKernelGGL(solve_begin_kernel, dim3((unsigned)n_occ + 1), dim3(1024), 0, s, slots, kt,
+                     n_occ, status, n_status);
+  return hipGetLastError();
 }
 
 int64_t solve_scratch_doubles(int ny_max, int dmax) {

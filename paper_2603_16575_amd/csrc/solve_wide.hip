@@ -189,13 +189,17 @@ void solve_wide_kernel(SolveArgs a) {
               }
             }
             if (GRAD && gpass) {
-              // this term alone, contracted with Y~ = 2Y - Y^T; R cleared again
+              // this term alone, contracted with Y~ = 2Y - Y^T, or (a diagonal
+              // source, whose mirror counts half and symmetrised) with
+              // (5Y - Y^T) / 4; R cleared again
+              const bool own = ti - f_tb < fdp->tx[tl];
+              const double wa = own ? 1.25 : 2.0, wb = own ? 0.25 : 1.0;
               __syncthreads();
               const double *Yc = Ycb + fdp->ysub[tl];
               const double *YTc = YTcb + fdp->ysub[tl];
               double part = 0.0;
               for (int e = tid; e < Dt * Dt; e += NTH) {
-                part += (2.0 * Yc[e] - YTc[e]) * R[e];
+                part += (wa * Yc[e] - wb * YTc[e]) * R[e];
                 R[e] = 0.0;
               }
               const double tot = wide_sum<NW>(part, red_d);
