@@ -10,6 +10,8 @@
 // coalesced) and each walks over a, so that the products of the first rounds
 // that do not depend on both (PhiloxColumn) are formed once per column, or on
 // the scalar unit, and no thread divides its element number into indices.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace mbe3 {
@@ -69,16 +71,17 @@ __device__ __forceinline__ double box_muller(uint64_t w0, uint64_t w1) {
 // the gradient probe direction Delta (stream 10); cb = 1, cd = t the shifted
 // slab B + t Delta of a finite-difference check.  cb and cd are uniform over
 // the launch, so the skipped draw is a uniform branch.
-// Workgroup (x, y, z): columns 256 x .., rows REGEN_ROWS y .., batch member z.
+// Workgroup (x, y, z): columns 256 x .., rows REGEN_ROWS (y0 + y) .., batch member z.
 constexpr int REGEN_ROWS = 16;
+constexpr int GRID_YZ = 65535;  // most workgroups of one launch along y or z
 __global__ __launch_bounds__(256) void regen_slab_kernel(
-    double *__restrict__ out, int i0, int n_vir, int n_aux,
+    double *__restrict__ out, int i0, int y0, int n_vir, int n_aux,
     uint64_t seed, const double *__restrict__ w_ia,
     const double *__restrict__ w_iP, double cb, double cd) {
   const int P = blockIdx.x * 256 + threadIdx.x;
   if (P >= n_aux) return;
   const int i = i0 + (int)blockIdx.z;
-  const int a0 = blockIdx.y * REGEN_ROWS, a1 = min(n_vir, a0 + REGEN_ROWS);
+  const int a0 = (y0 + (int)blockIdx.y) * REGEN_ROWS, a1 = min(n_vir, a0 + REGEN_ROWS);
   const double wp = w_iP[(int64_t)i * n_aux + P];
   const double *wa = w_ia + (int64_t)i * n_vir;
   double *o = out + (int64_t)blockIdx.z * n_vir * n_aux + P;
@@ -129,16 +132,16 @@ __device__ __forceinline__ void split3(double x, uint16_t *dst, int64_t ps) {
 // the transposed layout [b][P][a] (a fastest, row pitch ldk >= n_vir, zero
 // padded), the K-contiguous operand of the projection.  With an explicit
 // slab (device [n_occ][n_vir][n_aux]) its values are split instead.
-// Workgroup (x, y, z): rows a = 256 x .., columns REGEN_ROWS y .., member z; the
+// Workgroup (x, y, z): rows a = 256 x .., columns REGEN_ROWS (y0 + y) .., member z; the
 // column is uniform here, so its share of the generator is scalar work.
 __global__ __launch_bounds__(256) void regen_split_kernel(
-    uint16_t *__restrict__ planes, int64_t ps, int i0, int n_vir,
+    uint16_t *__restrict__ planes, int64_t ps, int i0, int y0, int n_vir,
     int n_aux, int ldk, uint64_t seed, const double *__restrict__ w_ia,
     const double *__restrict__ w_iP, const double *__restrict__ slab) {
   const int a = blockIdx.x * 256 + threadIdx.x;
   if (a >= ldk) return;
   const int i = i0 + (int)blockIdx.z;
-  const int P0 = blockIdx.y * REGEN_ROWS, P1 = min(n_aux, P0 + REGEN_ROWS);
+  const int P0 = (y0 + (int)blockIdx.y) * REGEN_ROWS, P1 = min(n_aux, P0 + REGEN_ROWS);
   const double wa = !slab && a < n_vir ? w_ia[(int64_t)i * n_vir + a] : 0.0;
   for (int P = P0; P < P1; ++P) {
     double x = 0.0;
@@ -212,16 +215,15 @@ hipError_t launch_regen_split(uint16_t *planes, int64_t ps, int i0, int nb,
                               int n_vir, int n_aux, int ldk, uint64_t seed,
                               const double *w_ia, const double *w_iP,
                               const double *slab, hipStream_t s) {
-  // batch members and column groups in launches of at most 65535
-  const int gy = (n_aux + REGEN_ROWS - 1) / REGEN_ROWS;
-  if (nb <= 0 || gy <= 0) return hipSuccess;
-  if (gy > 65535) return hipErrorInvalidValue;
-  for (int b = 0; b < nb; b += 65535)
-    hipLaunchKernelGGL(regen_split_kernel,
-                       dim3((unsigned)((ldk + 255) / 256), (unsigned)gy,
-                            (unsigned)(nb - b < 65535 ? nb - b : 65535)),
-                       dim3(256), 0, s, planes + (int64_t)b * n_aux * ldk, ps, i0 + b, n_vir,
-                       n_aux, ldk, seed, w_ia, w_iP, slab);
+  const int gy = (n_aux - 1) / REGEN_ROWS + 1;
+  if (nb <= 0 || n_aux <= 0 || ldk <= 0) return hipSuccess;
+  for (int b = 0; b < nb; b += GRID_YZ)
+    for (int y = 0; y < gy; y += GRID_YZ)
+      hipLaunchKernelGGL(regen_split_kernel,
+                         dim3((unsigned)((ldk - 1) / 256 + 1), (unsigned)std::min(gy - y, GRID_YZ),
+                              (unsigned)std::min(nb - b, GRID_YZ)),
+                         dim3(256), 0, s, planes + (int64_t)b * n_aux * ldk, ps, i0 + b, y, n_vir,
+                         n_aux, ldk, seed, w_ia, w_iP, slab);
   return hipGetLastError();
 }
 
@@ -248,15 +250,16 @@ hipError_t launch_split_rows_fixed(const double *x, int64_t rows, int cols, int6
 hipError_t launch_regen_slab(double *out, int i0, int nb, int n_vir, int n_aux,
                              uint64_t seed, const double *w_ia,
                              const double *w_iP, double cb, double cd, hipStream_t s) {
-  const int gy = (n_vir + REGEN_ROWS - 1) / REGEN_ROWS;
-  if (nb <= 0 || gy <= 0 || n_aux <= 0) return hipSuccess;
-  if (gy > 65535) return hipErrorInvalidValue;
-  for (int b = 0; b < nb; b += 65535)
-    hipLaunchKernelGGL(regen_slab_kernel,
-                       dim3((unsigned)((n_aux + 255) / 256), (unsigned)gy,
-                            (unsigned)(nb - b < 65535 ? nb - b : 65535)),
-                       dim3(256), 0, s, out + (int64_t)b * n_vir * n_aux, i0 + b, n_vir, n_aux,
-                       seed, w_ia, w_iP, cb, cd);
+  if (nb <= 0 || n_vir <= 0 || n_aux <= 0) return hipSuccess;
+  const int gy = (n_vir - 1) / REGEN_ROWS + 1;
+  for (int b = 0; b < nb; b += GRID_YZ)
+    for (int y = 0; y < gy; y += GRID_YZ)
+      hipLaunchKernelGGL(regen_slab_kernel,
+                         dim3((unsigned)((n_aux - 1) / 256 + 1),
+                              (unsigned)std::min(gy - y, GRID_YZ),
+                              (unsigned)std::min(nb - b, GRID_YZ)),
+                         dim3(256), 0, s, out + (int64_t)b * n_vir * n_aux, i0 + b, y, n_vir,
+                         n_aux, seed, w_ia, w_iP, cb, cd);
   return hipGetLastError();
 }
 
@@ -330,10 +333,10 @@ __global__ __launch_bounds__(256) void fit_mask_kernel(
 //   out[out_off[b] + a * nc + c] = B_i[a][cols[col_off[i] + c]],
 // each element regenerated exactly as regen_slab_kernel writes it (or read
 // from a given slab).  Workgroup (x, y, z): 64 kept columns, REGEN_ROWS rows for
-// each of its four waves, LMO z of the batch.
+// each of its four waves (from row group y0 on), LMO z of the batch.
 __global__ __launch_bounds__(256) void regen_cols_kernel(
     double *__restrict__ out, const int64_t *__restrict__ out_off,
-    const int32_t *__restrict__ cols, const int32_t *__restrict__ col_off, int i0,
+    const int32_t *__restrict__ cols, const int32_t *__restrict__ col_off, int i0, int y0,
     int n_vir, int n_aux, uint64_t seed, const double *__restrict__ w_ia,
     const double *__restrict__ w_iP, const double *__restrict__ slab) {
   const int i = i0 + (int)blockIdx.z;
@@ -342,7 +345,8 @@ __global__ __launch_bounds__(256) void regen_cols_kernel(
   if (c >= nc) return;
   const int P = cols[c0 + c];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int a0 = (blockIdx.y * 4 + wave) * REGEN_ROWS, a1 = min(n_vir, a0 + REGEN_ROWS);
+  const int a0 = ((y0 + (int)blockIdx.y) * 4 + wave) * REGEN_ROWS;
+  const int a1 = min(n_vir, a0 + REGEN_ROWS);
   double *o = out + out_off[blockIdx.z] + c;
   if (slab) {
     const double *b = slab + (int64_t)i * n_vir * n_aux + P;
@@ -382,12 +386,14 @@ hipError_t launch_regen_cols(double *out, const int64_t *out_off, const int32_t 
                              int n_vir, int n_aux, uint64_t seed, const double *w_ia,
                              const double *w_iP, const double *slab, hipStream_t s) {
   if (nb <= 0 || max_elems <= 0) return hipSuccess;
-  if (nb > 65535) return hipErrorInvalidValue;
+  if (nb > GRID_YZ) return hipErrorInvalidValue;
   const int64_t gx = (max_elems / n_vir + 63) / 64;  // max_elems: n_vir times the most columns
-  const int gy = (n_vir + 4 * REGEN_ROWS - 1) / (4 * REGEN_ROWS);
-  if (gy > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(regen_cols_kernel, dim3((unsigned)gx, (unsigned)gy, (unsigned)nb), dim3(256),
-                     0, s, out, out_off, cols, col_off, i0, n_vir, n_aux, seed, w_ia, w_iP, slab);
+  const int gy = (n_vir - 1) / (4 * REGEN_ROWS) + 1;
+  for (int y = 0; y < gy; y += GRID_YZ)
+    hipLaunchKernelGGL(regen_cols_kernel,
+                       dim3((unsigned)gx, (unsigned)std::min(gy - y, GRID_YZ), (unsigned)nb),
+                       dim3(256), 0, s, out, out_off, cols, col_off, i0, y, n_vir, n_aux, seed,
+                       w_ia, w_iP, slab);
   return hipGetLastError();
 }
 
@@ -429,7 +435,7 @@ hipError_t launch_regen_gauss(double *out, int i0, int nb, int n_rows, int n_vir
   const int gy = (n_rows + REGEN_ROWS - 1) / REGEN_ROWS;
   hipLaunchKernelGGL(regen_gauss_kernel,
                      dim3((unsigned)((n_vir + 255) / 256), (unsigned)gy,
-                          (unsigned)(nb < 65535 ? nb : 65535)),
+                          (unsigned)std::min(nb, GRID_YZ)),
                      dim3(256), 0, s, out, i0, nb, n_rows, n_vir, seed, stream);
   return hipGetLastError();
 }
