@@ -2299,8 +2299,12 @@ int mbe3_screen_lists(int32_t n_occ, const int32_t *pairs, int64_t n, const doub
       };
       if (!trimers) {
         for (size_t q = q0; q < q1; ++q) nt += keep(q);
-      } else if (nt + (int64_t)(q1 - q0) <= tri_cap) {  // every one written, the kept counted
-        for (size_t q = q0; q < q1; ++q) {
+      } else if (nt + (int64_t)(q1 - q0) <= tri_cap) {
+        // every one up to the last kept written, the kept counted: a rejected one is
+        // overwritten, and no branch depends on the metric
+        size_t qe = q1;
+        while (qe > q0 && !keep(qe - 1)) --qe;
+        for (size_t q = q0; q < qe; ++q) {
           trimers[3 * nt] = i;
           trimers[3 * nt + 1] = j;
           trimers[3 * nt + 2] = cl[q].j;
