@@ -98,7 +98,9 @@ struct mbe3_handle {
   int precision = MBE3_FP64;
   bool warm_start = false;
   double *warm = nullptr;  // converged Y of every slot's own fragment
-  double *base = nullptr;  // coupling sums of every dimer at those amplitudes
+  // coupling sums of every dimer at those amplitudes; null where there was no room
+  // for them (the trimers then form their own)
+  double *base = nullptr;
   std::vector<int64_t> base_off;
   int64_t base_total = 0;
   int ldk_vir = 0, ldk_aux = 0;  // padded row pitch of split planes
@@ -257,6 +259,12 @@ struct mbe3_handle {
       trim_call_pool(0);
       e = hipMalloc(p, bytes);
     }
+    if (e != hipSuccess && base && !recording && segs.empty()) {
+      (void)hipGetLastError();
+      (void)hipFree(base);  // waits for the launches that read it
+      base = nullptr;
+      e = hipMalloc(p, bytes);
+    }
     return e;
   }
   ~mbe3_handle() {
@@ -267,6 +275,7 @@ struct mbe3_handle {
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
     for (hipEvent_t e : event_pool) (void)hipEventDestroy(e);
     for (void *p : allocs) (void)hipFree(p);
+    if (base) (void)hipFree(base);
     trim_call_pool(0);
     if (h_status) (void)hipHostFree(h_status);
     if (h_e3) (void)hipHostFree(h_e3);
@@ -1272,7 +1281,6 @@ int alloc_workspace(mbe3_handle *h) {
   if ((rc = dev_alloc(h, &h->eig_meta, 4 * h->n_slot))) return rc;
   if ((rc = dev_alloc(h, &h->eig_redo, h->n_slot))) return rc;
   if (h->warm_start && (rc = dev_alloc(h, &h->warm, h->kt_off[h->n_slot]))) return rc;
-  if (h->base_total && (rc = dev_alloc(h, &h->base, h->base_total))) return rc;
   {
     const int md = max_d(h), nl = eig_lds_max_order();
     if (md > nl) {
@@ -1295,6 +1303,13 @@ int alloc_workspace(mbe3_handle *h) {
   if (h->dry) return MBE3_OK;
   HIP_TRY(h, hipHostMalloc((void **)&h->h_status, 2 * SOLVE_WG * sizeof(int32_t)));
   HIP_TRY(h, hipHostMalloc((void **)&h->h_e3, 4 * sizeof(double)));
+  if (h->base_total) {  // last: what the handle cannot do without comes first
+    void *q = nullptr;
+    if (h->device_malloc(&q, (size_t)h->base_total * sizeof(double)) == hipSuccess)
+      h->base = (double *)q;
+    else
+      (void)hipGetLastError();
+  }
   return MBE3_OK;
 }
 
