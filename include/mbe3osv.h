@@ -411,7 +411,8 @@ int64_t mbe3_screen_noalloc_max_bytes(void);
  * count; *sweeps (host) the sweeps run.  The pairs of one antidiagonal i + j
  * share no orbital and turn together, from the charges the pairs in order
  * would give them.  Allocates n_occ^2 doubles and, while P takes at most
- * 64 MiB, a second P per call, and synchronises `stream` after every sweep.
+ * 64 MiB and there is room, a second P per call, and synchronises `stream`
+ * after every sweep.
  * MBE3_EINVAL for bad sizes or offsets (message from mbe3_last_error(NULL)),
  * MBE3_ENOCONV when max_sweeps end above l_loc (outputs valid),
  * MBE3_ENONFINITE for a non-finite increment.

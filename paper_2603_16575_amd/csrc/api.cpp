@@ -2378,11 +2378,14 @@ int mbe3_pm_localize(const double *C, const int32_t *ao_off, int32_t n_ao, int32
   const int64_t nws = pm_ws_doubles(n_occ);
   hipError_t e = hipMalloc((void **)&d_off, sizeof(int32_t) * ((size_t)n_atom + 1));
   if (e == hipSuccess) e = hipMalloc((void **)&d_ws, sizeof(double) * (size_t)(nws + 2));
-  if (e == hipSuccess && pm_two_buffers(n_occ, n_atom)) e = hipMalloc((void **)&d_p2, p_bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     release();
     return fail(MBE3_ENOMEM, "mbe3_pm_localize: device allocation failed");
+  }
+  if (pm_two_buffers(n_occ, n_atom) && hipMalloc((void **)&d_p2, p_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    d_p2 = nullptr;  // no room: in place
   }
   e = hipMemcpyAsync(d_off, ao_off, sizeof(int32_t) * ((size_t)n_atom + 1),
                      hipMemcpyHostToDevice, st);

@@ -58,3 +58,23 @@ def test_coupling_sums_make_room(tmp_path):
         lib.mbe3_destroy(h)
         assert fake.fake_in_use() == 0
     """)
+
+
+def test_localization_without_a_second_buffer(tmp_path):
+    """Charges of up to 64 MiB move between two buffers; where the second does not fit
+    they are turned in place."""
+    _fake.run(tmp_path, """
+    n, na = 24, 18
+    C = np.zeros((n * 4, n)); off = np.arange(na + 1, dtype=np.int32); off[-1] = n * 4
+    P, U, ns = np.zeros((n, n, na)), np.zeros((n, n)), np.zeros(1, dtype=np.int32)
+    def call():
+        return lib.mbe3_pm_localize(ptr(C), ptr(off), n * 4, n, na, 1e-3, 5, ptr(P), ptr(U), None,
+                                    None, ptr(ns), None)
+    assert call() == 0 and fake.fake_asked(P.nbytes) == 1
+    assert fake.fake_launches(b"pm_step") == 2 * n - 3 and fake.fake_launches(b"pm_angle") == 0
+    fake.fake_refuse(P.nbytes)
+    assert call() == 0, lib.mbe3_last_error(None)
+    assert fake.fake_launches(b"pm_step") == 4 * n - 6
+    assert fake.fake_launches(b"pm_angle") == 2 * n - 3
+    assert ns[0] == 1 and fake.fake_in_use() == 0
+    """)
