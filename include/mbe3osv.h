@@ -37,8 +37,9 @@
  *     ABI.  The library allocates its own device workspace (at create and
  *     on first use); a handle keeps up to 512 MiB of what its allocating
  *     calls (screen, weak_pairs, project_fit, pair_K_fit, rosv) used for the
- *     next one, until it is destroyed or an allocation of its own fails.  It
- *     never frees or writes caller memory other than the documented outputs.
+ *     next one, until mbe3_release_blocks, until it is destroyed or until an
+ *     allocation of its own fails.  It never frees or writes caller memory
+ *     other than the documented outputs.
  *   - The handle is not thread safe; concurrent calls on one handle race.
  *
  * Index conventions:
@@ -170,6 +171,9 @@ typedef struct mbe3_layout {
    the device current at this call: its workspace is allocated there,
    `stream` must be that device's, and later calls on h expect it current. */
 int mbe3_create(mbe3_handle **h, const mbe3_problem *p, void *stream);
+/* Give back the device blocks that h keeps from finished allocating calls (for
+   the process's other allocators).  MBE3_EINVAL while recording. */
+int mbe3_release_blocks(mbe3_handle *h);
 /* Release the handle and its workspace (after finishing its stream). */
 int mbe3_destroy(mbe3_handle *h);
 /* Host string describing the last failure on h (never NULL). */

@@ -108,6 +108,11 @@ class Mbe3:
             _lib.load().mbe3_destroy(self._h)
             self._h = ctypes.c_void_p()
 
+    def release_blocks(self):
+        """Give back the device blocks kept from finished screen, weak_pairs,
+        project_fit, pair_K_fit and rosv calls (at most 512 MiB)."""
+        _lib.check(_lib.load().mbe3_release_blocks(self._h), self._h)
+
     def __del__(self):
         try:
             self.close()

@@ -36,7 +36,7 @@ EXPORTS = [
     "mbe3_tune_report", "mbe3_screen", "mbe3_weak_pairs", "mbe3_fit_metric",
     "mbe3_fit_mask", "mbe3_project_fit", "mbe3_pair_K_fit", "mbe3_first_order_dE",
     "mbe3_screen_lists", "mbe3_screen_noalloc", "mbe3_rosv", "mbe3_pm_localize",
-    "mbe3_set_slab_shift",
+    "mbe3_set_slab_shift", "mbe3_release_blocks",
 ]
 GEMM_SHAPES = ["64x64", "128x128", "32x32", "32x128", "64x128", "96x96"]
 PHASES = ["regen", "project", "pair_K", "bases", "pairs", "cross", "solve",
@@ -88,6 +88,7 @@ def load():
     sig = {
         "mbe3_create": [ctypes.POINTER(vp), ctypes.POINTER(Mbe3Problem), vp],
         "mbe3_destroy": [vp],
+        "mbe3_release_blocks": [vp],
         "mbe3_get_layout": [vp, ctypes.POINTER(Mbe3Layout)],
         "mbe3_gamma_offsets": [vp, vp],
         "mbe3_k_offsets": [vp, vp],

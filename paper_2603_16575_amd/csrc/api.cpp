@@ -2422,6 +2422,13 @@ int mbe3_pm_localize(const double *C, const int32_t *ao_off, int32_t n_ao, int32
   return MBE3_OK;
 }
 
+int mbe3_release_blocks(mbe3_handle *h) {
+  if (!h) return MBE3_EINVAL;
+  if (h->recording) return h->fail(MBE3_EINVAL, "mbe3_release_blocks while recording");
+  h->trim_call_pool(0);
+  return MBE3_OK;
+}
+
 int mbe3_destroy(mbe3_handle *h) {
   if (!h) return MBE3_EINVAL;
   if (h->recording) {
