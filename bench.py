@@ -67,17 +67,23 @@ def solve_flops(prob, iters, grad=False, warm=True):
     updates evaluates iters + 1 residuals; from T = 0 the first (R~ = K~)
     needs no product, so `iters` sweeps carry the products; a warm-started
     trimer's first residual has the products between its pairs (the last six
-    terms), while those within a pair's own fragment are formed once per dimer.
+    terms), while those within a pair's own fragment are formed once per pair, if
+    its trimers share pairs twice over and are at most 128 wide (else by each).
     With the gradient one term of each mirror couple goes through the products
     once more (dE/df)."""
     dims = fragment_dims(prob)
     tot = 0.0
-    sums = warm and len(prob.trimers) > 0
-    for f, terms, it in zip(prob.frags, dims, iters):
+    lds = [max([-(-dt // 16) * 16 for dt, _ in t], default=0) <= 128 for t in dims]
+    sides = [(f[a], f[b]) for f, ok in zip(prob.frags, lds) if ok and f[2] >= 0
+             for a, b in ((0, 1), (0, 2), (1, 2))]
+    summed = set(sides) if warm and len(sides) >= 2 * len(set(sides)) else set()
+    for f, terms, it, ok in zip(prob.frags, dims, iters, lds):
         fl = [2.0 * dt * ds * (ds + dt) for dt, ds in terms]
         per, warm_tri = sum(fl), warm and f[2] >= 0
-        tot += per * int(it) + (sum(fl[12:]) if warm_tri else 0.0)
-        if sums and f[1] >= 0 and f[2] < 0:
+        tot += per * int(it)
+        if warm_tri:
+            tot += sum(fl[12:]) if summed and ok else per
+        if f[2] < 0 and (f[0], f[1]) in summed:
             tot += per
         if grad and (int(it) > 0 or warm_tri):
             tot += 0.5 * per

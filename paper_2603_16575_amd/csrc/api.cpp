@@ -27,6 +27,11 @@ namespace {
 
 constexpr int DMAX_SUPPORTED = 160;  // largest padded pair dimension handled
 constexpr int SOLVE_WG = 1024;       // persistent workgroups of the solver
+// Trimers that share a pair, on average, from which the pairs' coupling sums are
+// formed once: 160 orbitals with random subsets of their trimers, solver time with
+// and without them 3.45 / 3.22 ms (1.1 trimers), 4.75 / 4.65 (1.5), 6.25 / 6.35 (2.1),
+// 9.35 / 9.96 (3.5), 16.0 / 17.5 (6.8), 88.6 / 100.4 (47).
+constexpr int64_t BASE_SHARE = 2;
 constexpr int64_t CLASS_MIN_FRAGS = 4096;  // fragments that make a solver class
 constexpr int64_t SLAB_BUDGET = 2LL << 30;    // bytes of regenerated slabs
 constexpr int64_t CHUNK_BUDGET = 12LL << 30;  // bytes of per-chunk stores
@@ -98,8 +103,8 @@ struct mbe3_handle {
   int precision = MBE3_FP64;
   bool warm_start = false;
   double *warm = nullptr;  // converged Y of every slot's own fragment
-  // coupling sums of every dimer at those amplitudes; null where there was no room
-  // for them (the trimers then form their own)
+  // coupling sums of the trimers' pairs at those amplitudes; null where they do not
+  // pay (BASE_SHARE) or there was no room (the trimers then form their own)
   double *base = nullptr;
   std::vector<int64_t> base_off;
   int64_t base_total = 0;
@@ -1186,17 +1191,30 @@ int build_plans(mbe3_handle *h) {
   if ((rc = dev_alloc(h, &h->st1, max_st1))) return rc;
 
   // ---- slots, energies ----
-  // coupling sums of the dimers whose domains the LDS-resident solver takes,
-  // where warm-started trimers read them
+  // coupling sums of the pairs of the warm-started trimers that the LDS-resident
+  // solver takes: the products that each trimer with the pair would form, so they
+  // save time where enough trimers share a pair
   h->base_off.assign(h->n_slot, -1);
   h->base_total = 0;
-  if (h->warm_start && !h->chunks.empty() && is_tri(h->chunks.back().frag_ids.front()))
-    for (int64_t s = n; s < h->n_slot; ++s) {
+  if (h->warm_start) {
+    std::vector<char> in_tri(h->n_slot, 0);
+    int64_t n_tri = 0, n_pairs = 0;
+    for (size_t m = 0; m < h->frags.size(); ++m) {
+      if (!is_tri((int)m) || fdim[m] > SOLVE_LDS_DMAX) continue;
+      const auto &o = h->frags[m];
+      ++n_tri;
+      for (int s : {slot_of(h, o[0], o[1]), slot_of(h, o[0], o[2]), slot_of(h, o[1], o[2])}) {
+        n_pairs += !in_tri[s];
+        in_tri[s] = 1;
+      }
+    }
+    for (int64_t s = n; s < h->n_slot && 3 * n_tri >= BASE_SHARE * n_pairs; ++s) {
+      if (!in_tri[s]) continue;
       const int64_t D = h->sD[s], Dp = h->sD[h->sp[s]], Dq = h->sD[h->sq[s]];
-      if (D > SOLVE_LDS_DMAX) continue;
       h->base_off[s] = h->base_total;
       h->base_total += Dp * Dp + Dq * Dq + D * D;
     }
+  }
   std::vector<SlotInfo> si(h->n_slot);
   for (int64_t s = 0; s < h->n_slot; ++s) {
     si[s].p = h->sp[s]; si[s].q = h->sq[s];
@@ -1609,9 +1627,8 @@ int validate_plans(mbe3_handle *h) {
           if (t.target != l) return bad("solve (term target)", k);
           if ((t.st_buf != 0) != (e >= fd.tx[l])) return bad("solve (cross terms)", k);
         }
-        if (fd.warm_in && dmax_of_chunk <= SOLVE_LDS_DMAX && l >= 3 &&
-            (h->base_off[fd.slot[l]] < 0 ||
-             h->base_off[fd.slot[l]] >= h->base_total))
+        if (h->base_total && fd.warm_in && dmax_of_chunk <= SOLVE_LDS_DMAX && l >= 3 &&
+            h->base_off[fd.slot[l]] < 0)
           return bad("solve (coupling sums)", k);
         at = fd.te[l];
         if (l + 1 == fd.nt && at != fd.term_end - fd.term_begin)
@@ -2590,7 +2607,7 @@ int fragment_solve(mbe3_handle *h, const double *K, double *e_frag,
     a.warm = h->warm;
     a.base = h->base;
     if (h->base && !base_done && h->frags[c.frag_ids.front()][2] >= 0) {
-      // every monomer and dimer is solved: their coupling sums, once per pair
+      // every monomer and dimer is solved: the coupling sums, once per pair
       for (auto &d : h->chunks) {
         if (h->frags[d.frag_ids.front()][2] >= 0 || d.dmax > SOLVE_LDS_DMAX) continue;
         SolveArgs g = a;

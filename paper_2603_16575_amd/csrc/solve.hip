@@ -212,9 +212,10 @@ __device__ __forceinline__ uint32_t part_mask(int part, int lg, int n) {
 // FragDesc::yout (zero if it converged at T = 0) for the gradient pass.
 // A warm-started trimer's first sweep reads the solutions of its pairs' own
 // fragments, so two thirds of its terms (a pair and one of its orbitals) depend
-// on the pair alone: MODE 3 forms those sums once per dimer, over the warm
+// on the pair alone: MODE 3 forms those sums once per pair, over the warm
 // store, and the trimers' first sweep adds them in its residual instead of
-// forming them again in each of the about 50 trimers of a pair.  At 160
+// forming them again in each of the pair's trimers (about 50; where it is less than
+// two, the planner leaves them out).  At 160
 // orbitals the solves take 119 ms instead of 136, the sums 0.43; at 96 orbitals
 // of 24 - 64 OSVs 135 instead of 152, the sums 0.67.
 // MODE 2: the gradient pass alone, a separate launch over the same
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void sol
     // fragment's own pairs (monomers, dimers), or after the first update
     bool hasY = false;
     if (GP && a.iters[f_frag] < 0) continue;  // uniform over the workgroup
-    if (BASE && f_nt != 3) continue;
+    if (BASE && (f_nt != 3 || a.slots[fdp->slot[2]].base_off < 0)) continue;
     // stage the descriptors (the previous fragment's last reads of them came
     // before its closing barrier)
     if (tid < f_te - f_tb) {

@@ -38,15 +38,14 @@ def explicit_df(ora, o, T):
     return g
 
 
-@pytest.mark.parametrize("warm", [False, True])
+@pytest.mark.parametrize("n,warm", [(3, False), (3, True), (4, True)])
 @pytest.mark.parametrize("r", [(2, 3), (9, 12), (23, 24), (30, 40), (41, 48), (49, 55),
                                (57, 64), (70, 78)])
-def test_unsymmetric_diagonal_blocks(m, r, warm):
+def test_unsymmetric_diagonal_blocks(m, r, n, warm):
     import torch
-    print(f"case: r {r}, warm start {warm}", flush=True)
-    prob = synth.micro(n_occ=3, n_vir=max(24, 4 * r[1]), n_aux=max(32, 5 * r[1]), r=r,
+    print(f"case: {n} LMOs, r {r}, warm start {warm}", flush=True)
+    prob = synth.micro(n_occ=n, n_vir=max(24, 4 * r[1]), n_aux=max(32, 5 * r[1]), r=r,
                        seed=10 * r[0] + r[1], tol=1e-9)
-    n = prob.n_occ
     h = m.from_problem(prob, device="cuda:0", warm_start=warm)
     K = h.pair_K(h.osv_project(h.empty_gamma()), h.empty_K())
     ora = oracle.Oracle(prob)
