@@ -1610,7 +1610,6 @@ int validate_plans(mbe3_handle *h) {
   for (size_t c = 0; c < h->h_fds.size(); ++c) {
     const auto &fds = h->h_fds[c];
     const auto &terms = h->h_terms[c];
-    const int dmax_of_chunk = h->chunks[c].dmax;
     for (size_t k = 0; k < fds.size(); ++k) {
       const FragDesc &fd = fds[k];
       if (!(fd.nt == 1 || fd.nt == 3 || fd.nt == 6)) return bad("solve (nt)", k);
@@ -1627,9 +1626,6 @@ int validate_plans(mbe3_handle *h) {
           if (t.target != l) return bad("solve (term target)", k);
           if ((t.st_buf != 0) != (e >= fd.tx[l])) return bad("solve (cross terms)", k);
         }
-        if (h->base_total && fd.warm_in && dmax_of_chunk <= SOLVE_LDS_DMAX && l >= 3 &&
-            h->base_off[fd.slot[l]] < 0)
-          return bad("solve (coupling sums)", k);
         at = fd.te[l];
         if (l + 1 == fd.nt && at != fd.term_end - fd.term_begin)
           return bad("solve (term ranges)", k);
@@ -1651,6 +1647,31 @@ int validate_plans(mbe3_handle *h) {
         const int64_t dt = h->sD[fd.slot[t.target]], ds = h->sD[fd.slot[t.src]];
         const int64_t lim = t.st_buf ? sz[B_ST1] : sz[B_ST0];
         if (t.st_off < 0 || t.st_off + ds * dt > lim) return bad("solve (S~ bounds)", k);
+      }
+    }
+  }
+  // coupling sums: a pair's three blocks inside the store, formed by a chunk of the
+  // LDS-resident solver ahead of the trimers that read them (all three pairs')
+  std::vector<char> formed(h->n_slot, 0);
+  for (size_t c = 0; c < h->h_fds.size() && h->base_total; ++c) {
+    if (h->chunks[c].dmax > SOLVE_LDS_DMAX) continue;
+    for (size_t k = 0; k < h->h_fds[c].size(); ++k) {
+      const FragDesc &fd = h->h_fds[c][k];
+      const int s = fd.slot[2];
+      if (fd.nt == 3 && h->base_off[s] >= 0) {
+        const int64_t D = h->sD[s], Dp = h->sD[h->sp[s]], Dq = h->sD[h->sq[s]];
+        if (fd.slot[0] != h->sp[s] || fd.slot[1] != h->sq[s] ||
+            h->base_off[s] + Dp * Dp + Dq * Dq + D * D > h->base_total)
+          return bad("solve (coupling sums)", k);
+        formed[s] = 1;
+      }
+      if (fd.nt == 6 && fd.warm_in) {
+        for (int l = 3; l < 6; ++l) {
+          const int t = fd.slot[l];
+          if (!formed[t] || h->sp[t] != fd.slot[l == 5 ? 1 : 0] ||
+              h->sq[t] != fd.slot[l == 3 ? 1 : 2])
+            return bad("solve (coupling sums of a trimer)", k);
+        }
       }
     }
   }
