@@ -2041,9 +2041,8 @@ static int weak_layout(mbe3_handle *h, const int32_t *pairs, int64_t n, bool ord
     g.m += w.ri;
     g.first.push_back(i);
   }
-  int64_t ko = 0, to = 0, rows = 0;
+  int64_t ko = 0, to = 0;
   for (WeakGroup &g : groups) {
-    rows += g.m;
     g.k_off = ko;
     g.t_off = to;
     ko += (int64_t)g.m * h->r[g.j];
@@ -2057,25 +2056,7 @@ static int weak_layout(mbe3_handle *h, const int32_t *pairs, int64_t n, bool ord
     w.t_off = g.t_off + row * w.Dj;
   }
   *k_tot = ko; *t_tot = to;
-  if (rows > 0x7fffffffLL)  // the row tables are indexed by 32 bits
-    return h->fail(MBE3_EINVAL, "too many pairs (%lld rows)", (long long)rows);
   return MBE3_OK;
-}
-
-// S_(i,j) = Q_i^T Q_j of every listed pair, one product per second LMO over the
-// gathered rows of its partners.
-static void weak_S_tasks(const mbe3_handle *h, const std::vector<WeakGroup> &groups,
-                         std::vector<GemmTask> &ts, std::vector<int32_t> &rows) {
-  const int nv = h->n_vir;
-  for (const WeakGroup &g : groups) {
-    const int rj = h->r[g.j];
-    GemmTask t = gemm(B_Q, 0, nv, 0, B_Q, h->q_off[g.j] * nv, nv, 1, B_PS2, g.k_off, rj, g.m,
-                      rj, nv);
-    t.a_rows = (int32_t)rows.size();
-    for (int i : g.first)
-      for (int mu = 0; mu < h->r[i]; ++mu) rows.push_back((int32_t)(h->q_off[i] + mu));
-    ts.push_back(t);
-  }
 }
 
 // One call-time task list: bounds-checked against sz and uploaded, ...
@@ -2111,6 +2092,48 @@ static int launch_call_list(mbe3_handle *h, const CallList &L, GemmBases b) {
   b.rows = L.d_rows;
   HIP_TRY(h, launch_gemm_tasks(L.d, L.n, L.tiles, b, L.shape, L.form, h->stream));
   return MBE3_OK;
+}
+
+// The products of all groups with rows gathered for their partners, uploaded as
+// lists of not much more than WEAK_LIST_ROWS rows each (the tables and tiles of a
+// list are counted in 32 bits, and its host copy is dropped when it is uploaded).
+// task(g) is group g's product, row(i) the first gathered row of LMO i.
+static const size_t WEAK_LIST_ROWS = 1 << 24;
+template <class Task, class Row>
+static int upload_gathered(mbe3_handle *h, CallTemp &tmp, std::vector<CallList> &L,
+                           const char *name, const std::vector<WeakGroup> &groups,
+                           const int64_t *sz, Task task, Row row) {
+  std::vector<GemmTask> ts;
+  std::vector<int32_t> rows;
+  for (size_t k = 0; k < groups.size(); ++k) {
+    GemmTask t = task(groups[k]);
+    t.a_rows = (int32_t)rows.size();
+    for (int i : groups[k].first)
+      for (int mu = 0; mu < h->r[i]; ++mu) rows.push_back((int32_t)(row(i) + mu));
+    ts.push_back(t);
+    if (rows.size() < WEAK_LIST_ROWS && k + 1 < groups.size()) continue;
+    L.emplace_back();
+    const int rc = upload_call_list(h, tmp, L.back(), name, ts, sz, GEMM_128x32, rows);
+    if (rc) return rc;
+    ts.clear();
+    rows.clear();
+  }
+  return MBE3_OK;
+}
+
+// S_(i,j) = Q_i^T Q_j of every listed pair, one product per second LMO over the
+// gathered rows of its partners.
+static int upload_weak_S(mbe3_handle *h, CallTemp &tmp, std::vector<CallList> &L,
+                         const char *name, const std::vector<WeakGroup> &groups,
+                         const int64_t *sz) {
+  const int nv = h->n_vir;
+  return upload_gathered(
+      h, tmp, L, name, groups, sz,
+      [&](const WeakGroup &g) {
+        return gemm(B_Q, 0, nv, 0, B_Q, h->q_off[g.j] * nv, nv, 1, B_PS2, g.k_off, h->r[g.j],
+                    g.m, h->r[g.j], nv);
+      },
+      [&](int i) { return h->q_off[i]; });
 }
 
 // No C++ exception crosses the C-ABI: host-side planning (containers, map
@@ -2896,18 +2919,15 @@ static int screen_body(mbe3_handle *h, const int32_t *pairs, int64_t n, double *
   double *S = nullptr;
   WeakPair *d_wp = nullptr;
   if ((rc = tmp.alloc(&S, ko)) || (rc = tmp.upload(&d_wp, wp))) return rc;
-  std::vector<GemmTask> ts;
-  std::vector<int32_t> rows;
-  weak_S_tasks(h, groups, ts, rows);
   int64_t sz[B_COUNT];
   base_sizes(h, sz);
   sz[B_PS2] = ko;
   GemmBases b = bases(h);
   b.p[B_PS2] = S;
-  CallList S_list;
-  if ((rc = upload_call_list(h, tmp, S_list, "screen S", ts, sz, GEMM_128x32, rows)) ||
-      (rc = launch_call_list(h, S_list, b)))
-    return rc;
+  std::vector<CallList> L;
+  if ((rc = upload_weak_S(h, tmp, L, "screen S", groups, sz))) return rc;
+  for (const CallList &l : L)
+    if ((rc = launch_call_list(h, l, b))) return rc;
   HIP_TRY(h, launch_s2b(d_wp, (int)n, S, s2b, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return MBE3_OK;
@@ -2937,26 +2957,18 @@ static int weak_body(mbe3_handle *h, const int32_t *pairs, int64_t n, const doub
       (rc = tmp.upload(&d_wp, wp)))
     return rc;
   const int na = h->n_aux;
-  std::vector<GemmTask> lk, ls, ltx, lbx, lkx, lsx, lsb;
-  std::vector<int32_t> rows_k, rows_s;
+  std::vector<GemmTask> ltx, lbx, lkx, lsx, lsb;
+  std::vector<int64_t> gam(h->n_occ, -1);  // gamma rows of block (i, i)
+  for (int i = 0; i < h->n_occ; ++i) {
+    const auto f = h->grow.find(key2(i, i));
+    if (f == h->grow.end())  // every LMO projects onto itself
+      return h->fail(MBE3_EINVAL, "internal: no gamma rows of (%d,%d)", i, i);
+    gam[i] = f->second;
+  }
   std::vector<char> left(h->n_occ, 0);
   for (const WeakGroup &g : groups) {
     const int j = g.j, rj = h->r[j], Dj = h->sD[j];
-    const auto fj = h->grow.find(key2(j, j));
-    if (fj == h->grow.end())  // every LMO projects onto itself
-      return h->fail(MBE3_EINVAL, "internal: no gamma rows of (%d,%d)", j, j);
-    // K_(i,j) = Gamma~_(i,i) Gamma~_(j,j)^T (eq. osv_weak_k) of all i of the group
-    GemmTask t = gemm(B_GAMMA, 0, na, 0, B_GAMMA, fj->second * na, na, 1, B_PK, g.k_off, rj,
-                      g.m, rj, na);
-    t.a_rows = (int32_t)rows_k.size();
-    for (int i : g.first) {
-      const auto fi = h->grow.find(key2(i, i));
-      if (fi == h->grow.end())
-        return h->fail(MBE3_EINVAL, "internal: no gamma rows of (%d,%d)", i, i);
-      for (int mu = 0; mu < h->r[i]; ++mu) rows_k.push_back((int32_t)(fi->second + mu));
-      left[i] = 1;
-    }
-    lk.push_back(t);
+    for (int i : g.first) left[i] = 1;
     // T_jj X_j (X: d x D, row-major; T_ii the diagonal slot blocks of W), then the
     // products with X_j and T_jj X_j from the right
     lbx.push_back(gemm(B_W, h->k_off[j], rj, 0, B_X, h->x_off[j], Dj, 0, B_PP, h->x_off[j], Dj,
@@ -2972,7 +2984,6 @@ static int weak_body(mbe3_handle *h, const int32_t *pairs, int64_t n, const doub
     if (left[i])  // T_ii^T X_i
       ltx.push_back(gemm(B_W, h->k_off[i], h->r[i], 1, B_X, h->x_off[i], h->sD[i], 0, B_PM,
                          h->x_off[i], h->sD[i], h->r[i], h->sD[i], h->r[i]));
-  weak_S_tasks(h, groups, ls, rows_s);
   int64_t sz[B_COUNT];
   base_sizes(h, sz);
   sz[B_W] = h->k_elems;
@@ -2985,14 +2996,24 @@ static int weak_body(mbe3_handle *h, const int32_t *pairs, int64_t n, const doub
   b.p[B_W] = const_cast<double *>(W);
   b.p[B_PK] = Kb; b.p[B_PS2] = Sb; b.p[B_PM] = TX; b.p[B_PP] = BX;
   b.p[B_PKT] = KX; b.p[B_PDT] = SX;
-  CallList L[7];
-  if ((rc = upload_call_list(h, tmp, L[0], "weak K", lk, sz, GEMM_128x32, rows_k)) ||
-      (rc = upload_call_list(h, tmp, L[1], "weak S", ls, sz, GEMM_128x32, rows_s)) ||
-      (rc = upload_call_list(h, tmp, L[2], "weak T^T X", ltx, sz, planned_shape(ltx))) ||
-      (rc = upload_call_list(h, tmp, L[3], "weak T X", lbx, sz, planned_shape(lbx))) ||
-      (rc = upload_call_list(h, tmp, L[4], "weak K X", lkx, sz, GEMM_128x32)) ||
-      (rc = upload_call_list(h, tmp, L[5], "weak S X", lsx, sz, GEMM_128x32)) ||
-      (rc = upload_call_list(h, tmp, L[6], "weak S T X", lsb, sz, GEMM_128x32)))
+  std::vector<CallList> L;
+  // K_(i,j) = Gamma~_(i,i) Gamma~_(j,j)^T (eq. osv_weak_k) of all i of a group
+  if ((rc = upload_gathered(
+           h, tmp, L, "weak K", groups, sz,
+           [&](const WeakGroup &g) {
+             return gemm(B_GAMMA, 0, na, 0, B_GAMMA, gam[g.j] * na, na, 1, B_PK, g.k_off,
+                         h->r[g.j], g.m, h->r[g.j], na);
+           },
+           [&](int i) { return gam[i]; })) ||
+      (rc = upload_weak_S(h, tmp, L, "weak S", groups, sz)))
+    return rc;
+  const size_t first = L.size();
+  L.resize(first + 5);
+  if ((rc = upload_call_list(h, tmp, L[first], "weak T^T X", ltx, sz, planned_shape(ltx))) ||
+      (rc = upload_call_list(h, tmp, L[first + 1], "weak T X", lbx, sz, planned_shape(lbx))) ||
+      (rc = upload_call_list(h, tmp, L[first + 2], "weak K X", lkx, sz, GEMM_128x32)) ||
+      (rc = upload_call_list(h, tmp, L[first + 3], "weak S X", lsx, sz, GEMM_128x32)) ||
+      (rc = upload_call_list(h, tmp, L[first + 4], "weak S T X", lsb, sz, GEMM_128x32)))
     return rc;
   // stream order: each list reads what the ones before it wrote
   for (const CallList &l : L)

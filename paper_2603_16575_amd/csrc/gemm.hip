@@ -510,7 +510,7 @@ hipError_t launch_gemm_tasks(const GemmTask *d_tasks, int n_tasks,
                              int64_t n_tiles, const GemmBases &bases,
                              GemmShape shape, int form, hipStream_t s) {
   if (n_tasks <= 0 || n_tiles <= 0) return hipSuccess;
-  if (n_tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (n_tiles >= 1 << 24) return hipErrorInvalidValue;  // a grid past 2^32 threads wraps
   const dim3 grid((unsigned)n_tiles);
   switch (shape) {
     case GEMM_64x64: return launch_shape<64, 64>(d_tasks, n_tasks, grid, bases, form, s);

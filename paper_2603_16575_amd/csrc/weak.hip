@@ -89,11 +89,16 @@ __global__ __launch_bounds__(256) void weak_energy_kernel(
   if (threadIdx.x == 0) e[blockIdx.x] = 4.0 * ((red[0] + red[1]) + (red[2] + red[3]));
 }
 
+// Pairs of one launch: a grid past 2^32 threads wraps without an error.
+static constexpr int PAIRS_MAX = 1 << 23;
+
 hipError_t launch_s2b(const WeakPair *wp, int n, const double *S, double *out,
                       hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(s2b_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, wp, n, S,
-                     out);
+  for (int k = 0; k < n; k += PAIRS_MAX) {
+    const int m = n - k < PAIRS_MAX ? n - k : PAIRS_MAX;
+    hipLaunchKernelGGL(s2b_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, wp + k, m, S,
+                       out + k);
+  }
   return hipGetLastError();
 }
 
@@ -101,9 +106,10 @@ hipError_t launch_weak_energy(const WeakPair *wp, int n, const double *X, const 
                               const double *KX, const double *SX, const double *et,
                               const int32_t *rank, const double *f, int n_occ, double *e,
                               hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(weak_energy_kernel, dim3((unsigned)n), dim3(256), 0, s, wp, X, TX, KX, SX,
-                     et, rank, f, n_occ, e);
+  for (int k = 0; k < n; k += PAIRS_MAX)
+    hipLaunchKernelGGL(weak_energy_kernel,
+                       dim3((unsigned)(n - k < PAIRS_MAX ? n - k : PAIRS_MAX)), dim3(256), 0, s,
+                       wp + k, X, TX, KX, SX, et, rank, f, n_occ, e + k);
   return hipGetLastError();
 }
 
