@@ -238,19 +238,15 @@ def cpu_baseline(prob, budget_workers, grad=False):
 
 
 def tune_choices(report):
-    """{list name: {"chosen": shape, "ms": {shape: ms per launch}}} from
-    mbe3_tune_report's lines."""
-    out = {}
+    """{"lists": how many, "chosen": {shape: lists}} from mbe3_tune_report's
+    lines (one per task list, with the time of every shape: Mbe3.autotune
+    returns them; over a hundred lists do not belong in the one JSON line)."""
+    chosen = {}
     for ln in report.splitlines():
-        if "->" not in ln:
-            continue
-        head, tail = ln.split(":", 1)
-        name = head.split(" ", 1)[1].rsplit(" (", 1)[0]
-        times, choice = tail.split("->")
-        tok = times.split()
-        ms = {tok[k]: float(tok[k + 1]) for k in range(0, len(tok) - 2, 3)}
-        out[name] = {"chosen": choice.split("(")[0].strip(), "ms": ms}
-    return out
+        if "->" in ln:
+            shape = ln.rsplit("->", 1)[1].split("(")[0].strip()
+            chosen[shape] = chosen.get(shape, 0) + 1
+    return {"lists": sum(chosen.values()), "chosen": chosen}
 
 
 def recorded_run(m, prob, args, dev, grad, label, steps=None, warmup=None, **kw):
