@@ -2303,7 +2303,8 @@ int mbe3_screen_lists(int32_t n_occ, const int32_t *pairs, int64_t n, const doub
     return fail("mbe3_screen_lists: bad arguments (n_occ %lld, n %lld)", n_occ, n);
   try {
     // normalised (i < j) pairs with their metric; the pairs seen so far in an
-    // open-addressing table at most half full
+    // open-addressing table at most half full (a list longer than the distinct
+    // pairs ends at a repeated one before that)
     struct Close {
       int32_t i, j;
       double v;
@@ -2311,7 +2312,8 @@ int mbe3_screen_lists(int32_t n_occ, const int32_t *pairs, int64_t n, const doub
     std::vector<Close> cl;
     std::vector<std::array<int32_t, 2>> wk;
     int bits = 4;
-    while (((int64_t)1 << bits) < 2 * n) ++bits;
+    const int64_t most = std::min<int64_t>(n, (int64_t)n_occ * (n_occ - 1) / 2 + 1);
+    while (((int64_t)1 << bits) < 2 * most) ++bits;
     std::vector<int64_t> seen((size_t)1 << bits, -1);  // pair index
     auto key_of = [&](int64_t k) {
       const int32_t a = pairs[2 * k], b = pairs[2 * k + 1];
@@ -2401,7 +2403,7 @@ int mbe3_screen_lists(int32_t n_occ, const int32_t *pairs, int64_t n, const doub
         for (size_t q = up[(size_t)i]; q <= p; ++q) with_i[(size_t)cl[q].j] = NAN;
     }
     *n_tri = nt;
-  } catch (const std::bad_alloc &) {
+  } catch (const std::exception &) {  // bad_alloc, length_error
     g_create_error = "mbe3_screen_lists: host allocation failed";
     return MBE3_ENOMEM;
   }
