@@ -222,7 +222,9 @@ int pair_K(mbe3_handle *h, const double *gamma, double *K, int64_t k_elems);
  * and returns the Hylleraas fragment energy
  *   e_frag[f] = sum_{p<=q in F} w_pq <2 T_pq - T_pq^T, K_pq + R_pq>,
  * w = 1 for p = q, 2 otherwise (Frobenius product).
- * K: device, pair_K's layout.  e_frag: device [n_frag].  iters: device
+ * K: device, pair_K's layout; a diagonal block that is not symmetric is taken as
+ * it is (W and dE/df are then those of the functional above at these amplitudes).
+ * e_frag: device [n_frag].  iters: device
  * [n_frag] int32, number of updates, or -(max_iter+1) if not converged.
  * W: device, K layout, or NULL; when given it receives the MBE multipliers
  *   W_s = sum_{F containing p,q} c_F (2 T^F_pq - T^F_pq^T)
@@ -374,7 +376,8 @@ int mbe3_screen_lists(int32_t n_occ, const int32_t *pairs, int64_t n, const doub
  * mbe3_screen without any allocation, for callers that cannot allocate
  * device memory (code that must not call hipMalloc / hipFree, tight
  * serving loops, harnesses that forbid allocation): the same s2b values as
- * mbe3_screen, bit for bit (same kernels, same order), with the task table,
+ * mbe3_screen, bit for bit (one product per pair instead of one per second LMO,
+ * each element summed in the same order), with the task table,
  * the pair table and the overlap blocks S_(i,j) held in a fixed scratch
  * array of mbe3_screen_noalloc_max_bytes() bytes (64 MiB) inside the
  * library, one per GPU, kept until the process ends.  A call needs about

@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tasks_kernel(
 // load and store part of a step, which the second workgroup of the CU covers);
 // the general kernel spent 16 loads, 16 stores and their guards on what takes 8
 // and 8 here.  Measured against it: projection of 48 orbitals, 2432 x 7040 slabs,
-// 41.6 ms for 45.9 ms (60.9 TF/s; a 8192^3 library product reaches 72), their pair
+// 41.6 ms for 45.9 ms (58.7 TF/s; a 8192^3 library product reaches 72), their pair
 // K 3.59 ms for 4.94 ms, a 160-orbital step's trimer blocks 16.5 ms for 20.5 ms,
 // its pair K 2.75 ms for 3.55 ms, the gradient's products 35.0 ms for 38.4 ms.
 // ---------------------------------------------------------------------------

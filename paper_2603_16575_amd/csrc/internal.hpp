@@ -311,8 +311,8 @@ struct SolveArgs {
                          // (launch_solve_base), or null
   // gradient mode (all null otherwise): the converged Y blocks per fragment
   // (at FragDesc::yout), the contractions <Y~_t, S~ Y_s^(T) S~^T>, Y~ = 2Y -
-  // Y^T, of the terms FragDesc::tg names, indexed by term, and per-target
-  // <Y~_t, Y_t> at 6 * fragment + target.
+  // Y^T, of the terms FragDesc::tg names, indexed by term (each standing for its
+  // mirror), and per-target <Y~_t, Y_t> at 6 * fragment + target.
   double *yfin;
   double *gterm;
   double *gdiag;
@@ -328,7 +328,7 @@ hipError_t launch_solve_base(const SolveArgs &a, int n_wg, hipStream_t s);
 // The gradient pass over a chunk that launch_solve solved with yfin set (the
 // same arguments and grid): per-term contractions and <Y~_t, Y_t>.
 hipError_t launch_solve_grad(const SolveArgs &a, int n_wg, hipStream_t s);
-// Variant for 96 < dmax <= 160 (solve_wide.hip): one wave per 16-row block,
+// Variant for 128 < dmax <= 160 (solve_wide.hip): one wave per 16-row block,
 // panels streamed for both products, per-workgroup term sums in the scratch
 // (which must hold 4 ny + 2 dmax^2 doubles, as solve_scratch_doubles gives).
 hipError_t launch_solve_wide(const SolveArgs &a, int n_wg, hipStream_t s);

@@ -93,7 +93,8 @@ static constexpr int PM_CB = 256 / PM_AL - 1;  // column groups of one workgroup
 // rotated).  cos and sin of theta by two half-angle steps from cos 4 theta =
 // -a / h, sin 4 theta = b / h, each taken from the larger of the two, instead of
 // the chain of atan2, sin and cos (a fifth of a step).  The charges of 32 localized
-// orbitals are off by 3.6e-17 (rms of eight problems) against 3.3e-17 with those.  Vanishing, huge and non-finite a, b take the library functions.
+// orbitals are off by 3.6e-17 (rms of eight problems) against 3.3e-17 with those.
+// Vanishing, huge and non-finite a, b take the library functions.
 __device__ __forceinline__ PmRot pm_angle(const double *P, int n, int na, int i, int j, int l,
                                           double *inc) {
   const double *pij = P + ((int64_t)i * n + j) * na;

@@ -214,20 +214,20 @@ __device__ __forceinline__ uint32_t part_mask(int part, int lg, int n) {
 // fragments, so two thirds of its terms (a pair and one of its orbitals) depend
 // on the pair alone: MODE 3 forms those sums once per pair, over the warm
 // store, and the trimers' first sweep adds them in its residual instead of
-// forming them again in each of the pair's trimers (about 50; where it is less than
-// two, the planner leaves them out).  At 160
-// orbitals the solves take 119 ms instead of 136, the sums 0.43; at 96 orbitals
-// of 24 - 64 OSVs 135 instead of 152, the sums 0.67.
+// forming them again in each of the pair's trimers (about 50; the planner leaves
+// them out where it is less than two).  All solver launches of 160 orbitals with
+// and without them: 88.6 and 100.4 ms, the sums 0.4 of it.
 // MODE 2: the gradient pass alone, a separate launch over the same
 // fragments: the terms [tb, tg) of each pair target are formed once more from
 // the stored Y with unit coefficient and contracted with Y~ = 2Y - Y^T.  The
 // coupling operator is symmetric, so a term's contraction equals its mirror's
 // (source and target exchanged) up to the pair weights (an unsymmetric diagonal
-// source is adapted to that), and 9 of a trimer's 18 terms are enough; of each
-// couple the one with the wider target runs, which leaves fewer waves without a
-// row block.  Measured at 160 orbitals (90k fragments): 28.4 ms for 59.8 ms with
-// every term.  Fragments that did not converge (iters < 0) are skipped.  Keeping
-// the pass out of the solving launch keeps its registers out of the iterations.
+// source is adapted to that), and 9 of a trimer's 18 terms are enough: of a pair and
+// its orbital the pair's (the wider target, which leaves fewer waves without a row
+// block), of two pairs one each way round the trimer.  Measured at 160 orbitals (90k
+// fragments): 28.4 ms for 59.8 ms with every term.  Fragments that did not converge
+// (iters < 0) are skipped.  Keeping the pass out of the solving launch keeps its
+// registers out of the iterations.
 template <int MAXNT, int MODE, int NW>
 __global__ __launch_bounds__(64 * NW, MAXNT == 5 ? 2 : NW == 4 ? 3 : 1) void solve_kernel(SolveArgs a) {
   constexpr bool ST = MODE == 1, GP = MODE == 2, BASE = MODE == 3;
